@@ -384,7 +384,7 @@ size_t epb_scratch_bytes(int32_t op, int32_t width, int32_t height, const void *
         if (!params) return 0;
         const epb_sphere_scene *sc = (const epb_sphere_scene *)params;
         if (sc->n < 0 || sc->n > EPB_MAX_SPHERES) return 0;
-        return align256((size_t)16 * (sc->n > 0 ? sc->n : 1));
+        return align256((size_t)epb::kSphereRecBytes * (sc->n > 0 ? sc->n : 1));
     }
     case EPB_OP_BLOOM_TONEMAP: {
         if (!params) return 0;
@@ -513,7 +513,7 @@ int epb_raycast(const epb_sphere_scene *scene, const epb_camera *cam, const epb_
         (attrs && (!aligned16(out->normal) || !aligned16(out->albedo) || !aligned16(out->roughness) ||
                    !aligned16(out->metalness))))
         return EPB_ERR_ALIGN;
-    size_t need = align256((size_t)16 * (scene->n > 0 ? scene->n : 1));
+    size_t need = align256((size_t)epb::kSphereRecBytes * (scene->n > 0 ? scene->n : 1));
     if (!scratch || scratch_bytes < need) return EPB_ERR_SCRATCH;
     if (!aligned16(scratch)) return EPB_ERR_ALIGN;
     epb::RayScene s{};
@@ -525,6 +525,7 @@ int epb_raycast(const epb_sphere_scene *scene, const epb_camera *cam, const epb_
     s.plane_rough = scene->plane_rough; s.plane_metal = scene->plane_metal;
     epb::RayCam c{};
     for (int k = 0; k < 12; ++k) c.M[k] = cam->world_to_cam[k];
+    for (int k = 0; k < 3; ++k) c.o[k] = -(c.M[k] * c.M[3] + c.M[4 + k] * c.M[7] + c.M[8 + k] * c.M[11]);
     c.fx = cam->fx; c.fy = cam->fy; c.cx = cam->cx; c.cy = cam->cy;
     c.W = cam->width; c.H = cam->height;
     epb::RayOut o{};

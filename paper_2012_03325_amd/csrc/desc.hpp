@@ -128,9 +128,11 @@ struct RayScene {
 };
 struct RayCam {
     double M[12];  // row-major [R | t]
+    double o[3];   // position, -R^T t
     double fx, fy, cx, cy;
     int W, H;
 };
+constexpr int kSphereRecBytes = 16;  // scratch per sphere
 struct RayOut {
     float *depth;
     void *normal, *albedo, *rough, *metal;  // null normal: depth only
