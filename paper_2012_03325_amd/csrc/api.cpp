@@ -86,7 +86,7 @@ int check_ibl_params(int S, const epb_ibl_params *p) {
 // ---- per-stage validation and descriptor set-up (shared by the single-view
 // calls and the batch builder) -------------------------------------------------
 int build_ssao(const epb_gbuffer *gbuf, const epb_camera *cam, const epb_ssao_params *params, void *ao_out,
-               void *scratch, size_t scratch_bytes, epb::SsaoDesc *out) {
+               void *scratch, size_t scratch_bytes, epb::SsaoDesc *out, bool in_batch = false) {
     if (!gbuf || !cam || !params || !ao_out) return EPB_ERR_NULL;
     int st = check_camera(cam);
     if (st) return st;
@@ -104,7 +104,7 @@ int build_ssao(const epb_gbuffer *gbuf, const epb_camera *cam, const epb_ssao_pa
     if (!aligned16(scratch)) return EPB_ERR_ALIGN;
     *out = epb::ssao_desc(plan, gbuf->depth, gbuf->normal, host_cam(cam), params->kernel, params->n_samples,
                           params->noise, params->radius, params->bias, params->blur_tau, params->blur ? 1 : 0,
-                          ao_out, scratch);
+                          ao_out, scratch, in_batch);
     return EPB_OK;
 }
 
@@ -565,6 +565,7 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
     // descriptors first (validating every view), then the header and item prefix sums
     epb::ViewDesc *vd = (epb::ViewDesc *)((char *)table + epb::batch_views_offset(n_views));
     char *sc = (char *)scratch;
+    int compact = 0;
     long long total[epb::kStages] = {}, chunks[epb::kStages] = {};
     int *start = (int *)((char *)table + epb::batch_start_offset());
     int *cstart = (int *)((char *)table + epb::batch_cstart_offset(n_views));
@@ -580,7 +581,8 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
         void *hdr = v.hdr ? v.hdr : (void *)(s_post + vs.post + vs.ao);
         epb::ViewDesc d;
         std::memset(&d, 0, sizeof(d));
-        if ((st = build_ssao(&v.gbuf, &v.cam, v.ssao, ao, s_ssao, vs.ssao, &d.ssao))) return st;
+        if ((st = build_ssao(&v.gbuf, &v.cam, v.ssao, ao, s_ssao, vs.ssao, &d.ssao, true))) return st;
+        if (d.ssao.hcompact) compact = 1;
         epb::ShadeArgs a;
         if ((st = build_shade(&v.gbuf, &v.cam, ao, v.ssao->out_dtype, v.lights, v.n_lights, v.ibl, v.env, hdr,
                               v.hdr_dtype, &a)))
@@ -634,6 +636,7 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
         start[k * (n_views + 1) + n_views] = (int)total[k];
         cstart[k * (n_views + 1) + n_views] = (int)chunks[k];
     }
+    h.compact = compact;
     h.persistent = q.persistent ? 1 : 0;
     h.chunk = q.persistent;
     h.gate = q.wait_limit < 0 ? 0 : 1;

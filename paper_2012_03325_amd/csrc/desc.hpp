@@ -59,7 +59,12 @@ struct SsaoDesc {
     const void *normal;
     const float *kernel;  // [n][3]
     const float *noise;   // [4][4][2]
-    float *hdepth;        // scratch: compact half-resolution depth
+    // half-resolution depth as the gathers read it: element (i, j) at byte
+    // (j hpitch + i) << hshift of hdepth, hcount elements in all
+    const float *hdepth;
+    int hpitch, hshift;
+    unsigned hcount;
+    float *hcompact;      // scratch for a compact copy, which hdepth then is; null: hdepth is `depth`
     void *raw;            // raw AO: scratch when blurred, else the output
     void *out;            // AO output
 };
@@ -186,6 +191,7 @@ struct BatchHeader {
     int gate;                       // 1; 0 makes every dependency wait give up (error-path tests)
     int total_chunks;
     int chunk_first[kStages + 1];   // first chunk of each stage
+    int compact;                    // some view takes a compact depth copy (else its stage is not launched)
 };
 
 // Work counters of the persistent launch, in the device copy of the table; the

@@ -46,7 +46,8 @@ struct SsaoPlan {
 SsaoPlan ssao_plan(int W, int H);
 SsaoDesc ssao_desc(const SsaoPlan &q, const float *depth, const void *normal, const HostCam &cam,
                    const float *kernel, int n_samples, const float *noise, float radius, float bias,
-                   float tau, int blur, void *ao_out, void *scratch);
+                   float tau, int blur, void *ao_out, void *scratch,
+                   bool in_batch);
 int ssao_items(const SsaoDesc &c, int stage, int ssao_tile);
 hipError_t launch_ssao(const SsaoDesc &c, epb_dtype gdtype, epb_dtype ao_dtype, hipStream_t s);
 hipError_t launch_ssao_batch(const BatchHeader &h, const void *table, hipStream_t s);

@@ -2,9 +2,10 @@
 // (paper Sec. 5.2: normal-oriented hemisphere, Bavoil and Sainz).
 //
 // gfx950 mapping:
-//  * prep compacts the half-resolution depth (the depth at (2i, 2j)) into a
-//    dense Wh x Hh plane: 2 MB at 1080p, resident in one XCD's 4 MB L2, so
-//    the sample gathers hit L2 instead of striding the full-resolution plane.
+//  * half-resolution depth is the depth at (2i, 2j).  Small images (see
+//    kSsaoDirectPixels) gather it from the full-resolution plane; for larger ones
+//    prep compacts it into a dense Wh x Hh plane first, so that the gathers keep
+//    hitting L2.
 //  * raw: one thread per half-resolution texel; the sample kernel is read with
 //    scalar loads (wave-uniform).  Every float decision is formed from small
 //    quantities, so that its rounding error does not grow with the depth or
@@ -22,8 +23,10 @@
 //    subtraction for z_q, one reciprocal, two fused offsets, two
 //    floor-converts, a range test, one gathered depth and 8 instructions of
 //    smoothstep and sum; gathers are issued a batch at a time before any is
-//    consumed, through a buffer resource whose range check makes an
-//    out-of-image offset read 0 (the sample is discarded by its range test).
+//    consumed, through a buffer resource of depth elements (the unit scales the
+//    index: one instruction less per sample, 30 us against 31 at 1920x1080 with
+//    64 samples) whose range check makes an out-of-image element read 0 (the
+//    sample is discarded by its range test).
 //  * blur: 4x4 bilateral mean; the 19x11 depth/AO footprint of a 16x8 tile is
 //    staged through LDS.
 //  * every stage has a single-view kernel (one block per tile, XCD-aware
@@ -115,6 +118,18 @@ __global__ void __launch_bounds__(kBlurTx *kBlurTy) k_ssao_blur_batch(const void
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
+// Largest image whose samples read the full-resolution depth, alone and as a
+// view of a batch.  The direct gathers touch twice the lines of a compact copy,
+// which an XCD's 4 MB L2 (it works on an eighth of the image) absorbs up to about
+// 3M pixels; the copy costs a launch and a pass.  SSAO with the blur, compact
+// against direct: 64 samples 1280x720 23.6 / 20.6 us, 1600x900 29.9 / 28.1,
+// 2048x1280 46.3 / 45.0, 2560x1440 62.0 / 64.8, 3840x2160 142 / 161.  Alone the
+// line is lower, since depth that has left the caches is fetched faster by the
+// copy's stream than by the gathers (1920x1080 frame with four 2048^2 maps: 122.8
+// / 124.2 us; 1003x667 59.7 / 57.2); in a batch the other views' tiles cover that
+// (16 views of up to 1920x1080, half storage: 387 / 375 us).
+constexpr size_t kSsaoDirectPixels = (size_t)3 << 19, kSsaoDirectBatchPixels = (size_t)3 << 20;
+
 SsaoPlan ssao_plan(int W, int H) {
     SsaoPlan q{};
     q.W = W;
@@ -142,7 +157,7 @@ int ssao_items(const SsaoDesc &c, int stage, int ssao_tile) {
 
 SsaoDesc ssao_desc(const SsaoPlan &q, const float *depth, const void *normal, const HostCam &cam, const float *kernel,
                    int n_samples, const float *noise, float radius, float bias, float tau, int blur, void *ao_out,
-                   void *scratch) {
+                   void *scratch, bool in_batch) {
     SsaoDesc c{};
     for (int k = 0; k < 9; ++k) c.cam.R[k] = cam.R[k];
     for (int k = 0; k < 3; ++k) c.cam.t[k] = cam.t[k];
@@ -161,7 +176,19 @@ SsaoDesc ssao_desc(const SsaoPlan &q, const float *depth, const void *normal, co
     c.kernel = kernel;
     c.noise = noise;
     char *sc = (char *)scratch;
-    c.hdepth = (float *)(sc + q.off_hdepth);
+    // small images: every second column and row of the full-resolution depth, no compact copy
+    if ((size_t)q.W * q.H <= (in_batch ? kSsaoDirectBatchPixels : kSsaoDirectPixels)) {
+        c.hdepth = depth;
+        c.hpitch = q.W;
+        c.hshift = 3;
+        c.hcount = ((unsigned)q.W * (unsigned)q.H + 1u) / 2u;  // the last one starts inside the plane
+    } else {
+        c.hcompact = (float *)(sc + q.off_hdepth);
+        c.hdepth = c.hcompact;
+        c.hpitch = q.Wh;
+        c.hshift = 2;
+        c.hcount = (unsigned)q.Wh * (unsigned)q.Hh;
+    }
     // raw AO goes to scratch when blurred, straight to the output otherwise
     c.raw = blur ? (void *)(sc + q.off_raw) : ao_out;
     c.out = ao_out;
@@ -176,7 +203,7 @@ static void go_raw(const SsaoDesc &c, hipStream_t s) {
 
 hipError_t launch_ssao(const SsaoDesc &c, epb_dtype gdtype, epb_dtype ao_dtype, hipStream_t s) {
     int prep = ssao_items(c, kStPrep, 0);
-    hipLaunchKernelGGL(k_ssao_prep, dim3(prep), dim3(kSsaoPrepW), 0, s, c, prep);
+    if (c.hcompact) hipLaunchKernelGGL(k_ssao_prep, dim3(prep), dim3(kSsaoPrepW), 0, s, c, prep);
     // the raw pass writes float32 into scratch when a blur follows
     epb_dtype raw_dt = c.blur ? EPB_F32 : ao_dtype;
     if (gdtype == EPB_F32) {
@@ -259,8 +286,9 @@ static void pick_raw_batch(const BatchHeader &h, const void *table, hipStream_t 
 }
 
 hipError_t launch_ssao_batch(const BatchHeader &h, const void *table, hipStream_t s) {
-    hipLaunchKernelGGL(k_ssao_prep_batch, dim3(batch_grid(h.total[kStPrep], h.blocks_per_cu)), dim3(kSsaoPrepW), 0,
-                       s, table);
+    if (h.compact)
+        hipLaunchKernelGGL(k_ssao_prep_batch, dim3(batch_grid(h.total[kStPrep], h.blocks_per_cu)), dim3(kSsaoPrepW), 0,
+                           s, table);
     epb_dtype raw_dt = h.blur ? EPB_F32 : (epb_dtype)h.ao_dtype;
     if (h.gdtype == EPB_F32) {
         if (raw_dt == EPB_F32) pick_raw_batch<float, float>(h, table, s);

@@ -11,12 +11,21 @@ namespace epb {
 // per-item work
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void ssao_prep_item(const SsaoDesc &c, int item) {
+    if (!c.hcompact) return;  // (uniform: a view of a batch that needs no copy)
     int chunks = (c.Wh + kSsaoPrepW - 1) / kSsaoPrepW;
     int j = item / chunks;
     int i = (item - j * chunks) * kSsaoPrepW + (int)threadIdx.x;
     if (i >= c.Wh) return;
-    stf(c.hdepth, __umul24((unsigned)j, (unsigned)c.Wh) + (unsigned)i,
+    stf(c.hcompact, __umul24((unsigned)j, (unsigned)c.Wh) + (unsigned)i,
         ldf(c.depth, __umul24((unsigned)(2 * j), (unsigned)c.W) + (unsigned)(2 * i)));
+}
+
+// Half-resolution depth (i, j), from the compact plane or the full-resolution one.
+__device__ __forceinline__ unsigned half_depth_index(const SsaoDesc &c, unsigned i, unsigned j) {
+    return __umul24(j, (unsigned)c.hpitch) + i;
+}
+__device__ __forceinline__ float half_depth(const SsaoDesc &c, unsigned i, unsigned j) {
+    return ldo(c.hdepth, half_depth_index(c, i, j) << c.hshift);
 }
 
 // Per-pixel constants of the sample loop: the kernel vector s enters through
@@ -28,7 +37,7 @@ struct SsaoPix {
 };
 
 // Half-resolution depth staged in LDS for a tile and its halo: lds[ly * kSsaoLdsW + lx]
-// holds texel (ox + lx, oy + ly) of the compact plane (clamped to the image:
+// holds texel (ox + lx, oy + ly) of the half-resolution depth (clamped to the image:
 // entries outside it are never used, a sample landing there is discarded).
 struct LdsWindow {
     const float *lds;
@@ -61,23 +70,23 @@ __device__ __forceinline__ float ssao_batch(const SsaoDesc &c, const ConstFloat 
         // (converted to 0) only arises with zq <= 0 or a NaN input, rejected by zq > 0)
         int ix = floor_to_int(fmaf(nx, iz, q.hx0)), iy = floor_to_int(fmaf(ny, iz, q.hy0));
         ok[b] = (!ragged || b < m) && zq > 0.0f && (unsigned)ix < (unsigned)c.Wh && (unsigned)iy < (unsigned)c.Hh;
-        // unchecked offset: when !ok it may point anywhere (a load past the plane
-        // reads 0, one inside it an unrelated texel) and the sample is discarded
-        off[b] = (__umul24((unsigned)iy, (unsigned)c.Wh) + (unsigned)ix) * 4u;
+        // unchecked element: when !ok it may point anywhere (a load past the plane
+        // reads 0, one inside it an unrelated depth) and the sample is discarded
+        off[b] = half_depth_index(c, (unsigned)ix, (unsigned)iy);
         if constexpr (kLds) {
             unsigned lx = (unsigned)(ix - win.ox), ly = (unsigned)(iy - win.oy);
             bool in = max(lx, ly) < (unsigned)kSsaoLdsW;
             ds[b] = win.lds[in ? __umul24(ly, (unsigned)kSsaoLdsW) + lx : 0u];
             miss |= ok[b] && !in;
         } else {
-            ds[b] = buf_ldf(hdepth, off[b]);
+            ds[b] = buf_ldf_at(hdepth, off[b]);
         }
         es[b] = e;
     }
     if constexpr (kLds) {
         if (miss) {
 #pragma unroll
-            for (int b = 0; b < KB; ++b) ds[b] = buf_ldf(hdepth, off[b]);
+            for (int b = 0; b < KB; ++b) ds[b] = buf_ldf_at(hdepth, off[b]);
         }
     }
 #pragma unroll
@@ -119,7 +128,7 @@ __device__ __forceinline__ float ssao_texel(const SsaoDesc &c, int i, int j, uns
     q.dpb = d + c.bias;
     q.hx0 = (float)i + 0.5f;
     q.hy0 = (float)j + 0.5f;
-    __amdgpu_buffer_rsrc_t hdepth = raw_buffer(c.hdepth, (unsigned)c.Wh * (unsigned)c.Hh * 4u);
+    __amdgpu_buffer_rsrc_t hdepth = element_buffer(c.hdepth, 1 << c.hshift, c.hcount);
     float occ = 0.0f;
     // whole batches of KB samples (their 3 KB kernel floats in one run of scalar
     // loads), then the ragged last batch with its sample index clamped
@@ -163,7 +172,7 @@ __device__ __forceinline__ void ssao_raw_tile_lds(const SsaoDesc &c, int tile, f
         int q = (int)threadIdx.x + NT * k;
         int ly = q / kSsaoLdsW, lx = q - ly * kSsaoLdsW;
         int gi = min(max(win.ox + lx, 0), c.Wh - 1), gj = min(max(win.oy + ly, 0), c.Hh - 1);
-        st[k] = ldf(c.hdepth, __umul24((unsigned)gj, (unsigned)c.Wh) + (unsigned)gi);
+        st[k] = half_depth(c, (unsigned)gi, (unsigned)gj);
     }
     __syncthreads();
 #pragma unroll
@@ -204,9 +213,9 @@ __device__ __forceinline__ void ssao_blur_tile(const SsaoDesc &c, int tile, floa
         int li = q % LW, lj = q / LW;
         int gi = i0 + li - 2, gj = j0 + lj - 2;
         in[k] = gi >= 0 && gi < c.Wh && gj >= 0 && gj < c.Hh;
-        unsigned g = in[k] ? __umul24((unsigned)gj, (unsigned)c.Wh) + (unsigned)gi : 0u;
-        dq[k] = ldf(c.hdepth, g);
-        aq[k] = ldf(raw, g);
+        unsigned ci = in[k] ? (unsigned)gi : 0u, cj = in[k] ? (unsigned)gj : 0u;
+        dq[k] = half_depth(c, ci, cj);
+        aq[k] = ldf(raw, __umul24(cj, (unsigned)c.Wh) + ci);
     }
 #pragma unroll
     for (int k = 0; k < kIt; ++k) {  // unconditional: entries past the footprint land in the padding rows
