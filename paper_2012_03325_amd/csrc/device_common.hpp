@@ -341,6 +341,23 @@ __device__ __forceinline__ XcdRange xcd_range(int total) {
     return w;
 }
 
+// The shading pass's order: chunks of kShadeChunk consecutive items go to the XCDs
+// in turn, so that every XCD gets its share of the costly rows (a contiguous
+// eighth of the image leaves the XCDs of the sky idle) while neighbouring tiles
+// still share an L2; what does not fill a round of chunks is split as above.
+// Item `it` of XCD x (0 <= it < xcd_chunk_count):
+constexpr int kShadeChunk = 64;
+__device__ __forceinline__ int xcd_chunk_item(int x, int it, int total) {
+    int rounds = total / (kNumXcd * kShadeChunk);
+    if (it < rounds * kShadeChunk) return (it / kShadeChunk * kNumXcd + x) * kShadeChunk + it % kShadeChunk;
+    int first = rounds * (kNumXcd * kShadeChunk), rest = total - first;
+    int q = rest / kNumXcd, r = rest % kNumXcd;
+    return first + x * q + min(x, r) + (it - rounds * kShadeChunk);
+}
+__device__ __forceinline__ int xcd_chunk_count(int x, int total) {
+    return total / kNumXcd + (x < total % kNumXcd ? 1 : 0);
+}
+
 // View owning work item g: start[v] <= g < start[v + 1] (binary search; uniform).
 __device__ __forceinline__ int find_view(const int *start, int n, int g) {
     int lo = 0, hi = n;
