@@ -80,58 +80,68 @@ __device__ __forceinline__ float segment_sum_compensated(float v, int width) {
 // add, this equals repeated 2x2 weighted halving.  Also writes the source
 // table entry (unit direction, solid angle at size Ss).
 // A segment of lpt lanes (the k x k block rounded up to a power of two, at most
-// 64) per source texel: each lane sums its share of the block with Kahan, the
-// segment adds the lanes' sums compensated.  lpt is uniform.
-__global__ void __launch_bounds__(256) k_ibl_source(const float4 *__restrict__ env, int S, int Ss, int lpt,
-                                                    float4 *__restrict__ src, float4 *__restrict__ tab) {
-    int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+// 64) per texel (i, j), for all six faces: a solid angle, most of the work, does
+// not depend on the face (6x512^2: 31 us with a segment per face).  Each lane
+// sums its share of the block with Kahan, the segment adds the lanes' sums
+// compensated.  lpt is uniform.
+__device__ __forceinline__ void ibl_source_block(int block, const float4 *__restrict__ env, int S, int Ss, int lpt,
+                                                 float4 *__restrict__ src, float4 *__restrict__ tab) {
+    int t = block * 256 + (int)threadIdx.x;
     int o = t / lpt, sub = t - o * lpt;
-    int nsrc = 6 * Ss * Ss;
-    // (the segment stays together: nsrc * lpt threads fill whole segments)
-    bool live = o < nsrc;
-    int oc = live ? o : nsrc - 1;
-    int f = oc / (Ss * Ss), j = (oc / Ss) % Ss, i = oc % Ss;
+    int nface = Ss * Ss;
+    // (the segment stays together: nface * lpt threads fill whole segments)
+    bool live = o < nface;
+    int oc = live ? o : nface - 1;
+    int j = oc / Ss, i = oc - j * Ss;
     int k = S / Ss;
-    Kahan r{0, 0}, g{0, 0}, b{0, 0}, w{0, 0};
-    const float4 *face = env + (size_t)f * S * S;
+    Kahan w{0, 0};
+    Kahan c[6][3] = {};
     for (int q = sub; q < k * k; q += lpt) {
         int bj = q / k, bi = q - bj * k;
         int ci = i * k + bi, cj = j * k + bj;
+        float4 L[6];
+#pragma unroll
+        for (int f = 0; f < 6; ++f) L[f] = env[(size_t)f * S * S + (size_t)cj * S + ci];
         float dw = k == 1 ? 1.0f : texel_solid_angle(ci, cj, S);
-        float4 L = face[(size_t)cj * S + ci];
-        kahan_add(r, L.x * dw);
-        kahan_add(g, L.y * dw);
-        kahan_add(b, L.z * dw);
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+            kahan_add(c[f][0], L[f].x * dw);
+            kahan_add(c[f][1], L[f].y * dw);
+            kahan_add(c[f][2], L[f].z * dw);
+        }
         kahan_add(w, dw);
     }
-    float R = segment_sum_compensated(kahan_value(r), lpt);
-    float G = segment_sum_compensated(kahan_value(g), lpt);
-    float Bv = segment_sum_compensated(kahan_value(b), lpt);
-    float W = segment_sum_compensated(kahan_value(w), lpt);
-    if (live && sub == 0) {
-        float iw = 1.0f / W;
-        src[o] = make_float4(R * iw, G * iw, Bv * iw, 0.0f);
-        v3 d = normalize(cube_texel_dir(f, i, j, Ss));
-        tab[o] = make_float4(d.x, d.y, d.z, texel_solid_angle(i, j, Ss));
+    float iw = 1.0f / segment_sum_compensated(kahan_value(w), lpt);
+    float dw = texel_solid_angle(i, j, Ss);
+#pragma unroll
+    for (int f = 0; f < 6; ++f) {
+        float R = segment_sum_compensated(kahan_value(c[f][0]), lpt);
+        float G = segment_sum_compensated(kahan_value(c[f][1]), lpt);
+        float Bv = segment_sum_compensated(kahan_value(c[f][2]), lpt);
+        if (live && sub == 0) {
+            src[f * nface + o] = make_float4(R * iw, G * iw, Bv * iw, 0.0f);
+            v3 d = normalize(cube_texel_dir(f, i, j, Ss));
+            tab[f * nface + o] = make_float4(d.x, d.y, d.z, dw);
+        }
     }
 }
 
-// Partial irradiance sums over source chunk blockIdx.y for 256 outputs.
+// Partial irradiance sums over source chunk `chunk` for 256 outputs; `lds` holds
+// two blocks of 256 float4.
 // part layout: [chunk][output][8] = Kahan (s, c) of R, G, B, weight.
-__global__ void __launch_bounds__(256) k_irradiance_partial(const float4 *__restrict__ src,
-                                                            const float4 *__restrict__ tab, int nsrc,
-                                                            int chunk_len, int irr, float *__restrict__ part) {
-    __shared__ float4 sL[256];
-    __shared__ float4 sT[256];
+__device__ __forceinline__ void irradiance_partial_block(int block, int chunk, const float4 *__restrict__ src,
+                                                         const float4 *__restrict__ tab, int nsrc, int chunk_len,
+                                                         int irr, float *__restrict__ part, float4 *lds) {
+    float4 *sL = lds, *sT = lds + 256;
     int nout = 6 * irr * irr;
-    int o = blockIdx.x * 256 + threadIdx.x;
+    int o = block * 256 + threadIdx.x;
     v3 n = mk3(0, 0, 1);
     if (o < nout) {
         int f = o / (irr * irr), j = (o / irr) % irr, i = o % irr;
         n = normalize(cube_texel_dir(f, i, j, irr));
     }
     Kahan r{0, 0}, g{0, 0}, b{0, 0}, w{0, 0};
-    int beg = blockIdx.y * chunk_len;
+    int beg = chunk * chunk_len;
     int end = min(beg + chunk_len, nsrc);
     for (int base = beg; base < end; base += 256) {
         int t = base + threadIdx.x;
@@ -174,53 +184,111 @@ __global__ void __launch_bounds__(256) k_irradiance_partial(const float4 *__rest
         __syncthreads();
     }
     if (o < nout) {
-        float *p = part + ((size_t)blockIdx.y * nout + o) * 8;
+        float *p = part + ((size_t)chunk * nout + o) * 8;
         p[0] = r.s; p[1] = g.s; p[2] = b.s; p[3] = w.s;
         p[4] = r.c; p[5] = g.c; p[6] = b.c; p[7] = w.c;
     }
 }
 
-__global__ void __launch_bounds__(256) k_irradiance_final(const float *__restrict__ part, int chunks,
-                                                          int irr, float4 *__restrict__ out) {
-    int nout = 6 * irr * irr;
-    int o = blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= nout) return;
-    Kahan acc[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
+// Sums of the chunks' partials, one lane per component of an output (four lanes
+// side by side: their serial compensated adds run beside each other).
+__device__ __forceinline__ void irradiance_final_block(int block, const float *__restrict__ part, int chunks, int nout,
+                                                       float4 *__restrict__ out) {
+    int t = block * 256 + (int)threadIdx.x;
+    int o = t >> 2, q = t & 3;
+    bool live = o < nout;
+    Kahan acc{0, 0};
+    const float *p = part + (size_t)(live ? o : 0) * 8 + q;
     // (unrolled: several chunks' loads in flight ahead of the serial adds)
 #pragma unroll 8
     for (int c = 0; c < chunks; ++c) {
-        const float *p = part + ((size_t)c * nout + o) * 8;
-        for (int q = 0; q < 4; ++q) {
-            kahan_add(acc[q], p[q]);
-            kahan_add(acc[q], -p[4 + q]);
-        }
+        float v = p[(size_t)c * nout * 8], e = p[(size_t)c * nout * 8 + 4];
+        kahan_add(acc, v);
+        kahan_add(acc, -e);
     }
-    float iw = 1.0f / kahan_value(acc[3]);
-    out[o] = make_float4(kahan_value(acc[0]) * iw, kahan_value(acc[1]) * iw, kahan_value(acc[2]) * iw, 0.0f);
+    float v = kahan_value(acc);
+    float iw = 1.0f / __shfl(v, (int)(threadIdx.x & 63) | 3, 64);  // the weight's lane
+    if (live) ((float *)out)[(size_t)o * 4 + q] = q < 3 ? v * iw : 0.0f;
 }
 
 // Roughness-0 level: the environment along each texel direction.
-__global__ void __launch_bounds__(256) k_prefilter_mirror(const float4 *__restrict__ env, int S, int sm,
-                                                          float4 *__restrict__ out) {
-    int o = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void prefilter_mirror_block(int block, const float4 *__restrict__ env, int S, int sm,
+                                                       float4 *__restrict__ out) {
+    int o = block * 256 + (int)threadIdx.x;
     if (o >= 6 * sm * sm) return;
     int f = o / (sm * sm), j = (o / sm) % sm, i = o % sm;
     v3 n = normalize(cube_texel_dir(f, i, j, sm));
     out[o] = cube_bilinear(env, face_dims(S), n);
 }
 
-// Environment mip chain for filtered importance sampling.  Level 0 is a copy
-// of the environment so that every level sits at a closed-form offset of one
-// buffer: level k (faces S >> k, S a power of two) starts at texel
-// 8 (S^2 - (S >> k)^2) = 6 (S^2 + (S/2)^2 + ... + (S >> (k-1))^2).
-__device__ __forceinline__ unsigned chain_offset_pow2(int S, int k) {
+// Environment mip chain for filtered importance sampling: levels 1 .. last of one
+// buffer (level 0 is the environment itself), level k (faces S >> k, S a power of
+// two) at texel 2 S^2 - 8 (S >> k)^2 = 6 ((S/2)^2 + ... + (S >> (k-1))^2).
+__host__ __device__ inline unsigned chain_offset_pow2(int S, int k) {
     unsigned s = (unsigned)S, sk = (unsigned)(S >> k);
-    return 8u * (s * s - sk * sk);
+    return 2u * s * s - 8u * sk * sk;
 }
 
-__global__ void __launch_bounds__(256) k_env_copy(const float4 *__restrict__ env, int n, float4 *__restrict__ dst) {
-    int o = blockIdx.x * blockDim.x + threadIdx.x;
-    if (o < n) dst[o] = env[o];
+// The solid-angle-weighted mean of the 2x2 children L of texel (i, j) of a level
+// whose parent level has faces of size Sp, as the irradiance source is built.
+__device__ __forceinline__ float4 mean_of_children(const float4 (&L)[4], const float (&dw)[4]) {
+    float r = 0.0f, g = 0.0f, b = 0.0f, w = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        r = fmaf(L[q].x, dw[q], r);
+        g = fmaf(L[q].y, dw[q], g);
+        b = fmaf(L[q].z, dw[q], b);
+        w += dw[q];
+    }
+    float iw = 1.0f / w;
+    return make_float4(r * iw, g * iw, b * iw, 0.0f);
+}
+
+// Up to five chain levels in one launch: a block takes the 32 x 32 texels (or the
+// whole face) at its place of level `first` of all six faces (the solid angles do
+// not depend on the face) and writes what it covers of the levels below it, each
+// from the one before in LDS.
+constexpr int kChainStep = 5;
+struct ChainLds {
+    float4 a[6 * 16 * 16], b[6 * 8 * 8];
+};
+__device__ __forceinline__ void env_chain_block(int block, const float4 *__restrict__ env, float4 *__restrict__ chain,
+                                                int S, int first, int last, ChainLds &sm) {
+    int Sp = S >> first;
+    const float4 *src = first == 0 ? env : chain + chain_offset_pow2(S, first);
+    int side = min(Sp, 32);  // a power of two
+    int across = Sp / side;
+    int by = block / across, bx = block - by * across;
+    float4 *from = nullptr, *to = sm.a;
+    int t = (int)threadIdx.x;
+    for (int k = first + 1; k <= min(first + kChainStep, last); ++k) {
+        int n = side >> (k - first), Sd = S >> k;  // this block's n x n texels of level k
+        float4 *out = chain + chain_offset_pow2(S, k);
+        int each = from ? 1 : 6;  // faces per thread: all six where the children come from memory
+        for (int q = t; q < n * n * (6 / each); q += 256) {
+            int f0 = q / (n * n), r = q - f0 * n * n;
+            int ly = r / n, lx = r - ly * n;
+            int i = bx * n + lx, j = by * n + ly;
+            float dw[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) dw[c] = texel_solid_angle(2 * i + (c & 1), 2 * j + (c >> 1), 2 * Sd);
+            for (int e = 0; e < each; ++e) {
+                int f = f0 + e;
+                float4 L[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    L[c] = from ? from[(f * 2 * n + 2 * ly + (c >> 1)) * 2 * n + 2 * lx + (c & 1)]
+                                : src[((size_t)f * Sp + 2 * j + (c >> 1)) * Sp + 2 * i + (c & 1)];
+                float4 v = mean_of_children(L, dw);
+                out[((size_t)f * Sd + j) * Sd + i] = v;
+                to[(f * n + ly) * n + lx] = v;
+            }
+        }
+        __syncthreads();
+        from = to;
+        to = to == sm.a ? sm.b : sm.a;
+        // (the next level's texels fit the other array: 6 n^2 / 4 of them; it is read no more)
+    }
 }
 
 // Level 0 of the environment as packed RGB texels (12 bytes) for the
@@ -229,8 +297,9 @@ __global__ void __launch_bounds__(256) k_env_copy(const float4 *__restrict__ env
 struct Rgb {
     float r, g, b;
 };
-__global__ void __launch_bounds__(256) k_env_rgb(const float4 *__restrict__ env, int n, Rgb *__restrict__ dst) {
-    int o = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void env_rgb_block(int block, const float4 *__restrict__ env, int n,
+                                              Rgb *__restrict__ dst) {
+    int o = block * 256 + (int)threadIdx.x;
     if (o < n) {
         float4 v = env[o];
         sto(dst, (unsigned)o * 12u, Rgb{v.x, v.y, v.z});
@@ -265,32 +334,7 @@ __device__ __forceinline__ float4 rgb_bilinear(const RgbTaps &q) {
     return lerp4(lerp4(A, B, q.wx), lerp4(C, D, q.wx), q.wy);
 }
 
-// Level k from level k - 1 (face size Sp = 2 Sd): solid-angle-weighted mean of
-// the 2x2 children, as the irradiance source is built.
-__global__ void __launch_bounds__(256) k_env_down(const float4 *__restrict__ src, int Sp,
-                                                  float4 *__restrict__ dst) {
-    int Sd = Sp >> 1;
-    int o = blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= 6 * Sd * Sd) return;
-    int f = o / (Sd * Sd), j = (o / Sd) % Sd, i = o % Sd;
-    const float4 *face = src + (size_t)f * Sp * Sp;
-    float r = 0.0f, g = 0.0f, b = 0.0f, w = 0.0f;
-    for (int bj = 0; bj < 2; ++bj)
-        for (int bi = 0; bi < 2; ++bi) {
-            int ci = 2 * i + bi, cj = 2 * j + bj;
-            float dw = texel_solid_angle(ci, cj, Sp);
-            float4 L = face[(size_t)cj * Sp + ci];
-            r = fmaf(L.x, dw, r);
-            g = fmaf(L.y, dw, g);
-            b = fmaf(L.z, dw, b);
-            w += dw;
-        }
-    float iw = 1.0f / w;
-    dst[o] = make_float4(r * iw, g * iw, b * iw, 0.0f);
-}
-
-// The GGX samples of the prefiltered levels (one launch, blockIdx.y = level):
-// entry k of level m is the tangent-frame half vector of Hammersley sample k for
+// The GGX samples of the prefiltered levels: entry k of level m is the tangent-frame half vector of Hammersley sample k for
 // roughness^2 = alpha_m and, for filtered importance sampling, the environment
 // chain level that sample reads (w; 0 otherwise).  That level is lod0 - log2(den)
 // clamped to [0, last], where den = (1 - u2) + alpha^2 u2 is the GGX sampling
@@ -301,9 +345,9 @@ __global__ void __launch_bounds__(256) k_env_down(const float4 *__restrict__ src
 struct GgxLevels {
     float alpha[8], lod0[8];
 };
-__global__ void __launch_bounds__(256) k_ggx_table(GgxLevels lv, int samples, int fis, int last,
-                                                   float4 *__restrict__ tables) {
-    int k = (int)blockIdx.x * 256 + (int)threadIdx.x, m = (int)blockIdx.y;
+__device__ __forceinline__ void ggx_table_block(int block, int m, const GgxLevels &lv, int samples, int fis, int last,
+                                                float4 *__restrict__ tables) {
+    int k = block * 256 + (int)threadIdx.x;
     float alpha = lv.alpha[m];
     if (k >= samples || alpha == 0.0f) return;
     float a2 = alpha * alpha;
@@ -324,13 +368,13 @@ __global__ void __launch_bounds__(256) k_ggx_table(GgxLevels lv, int samples, in
 // lookups' taps are in flight before either is added (the adds keep the order
 // k, k + 64, k + 128, ...), and the next pair's table entries load one
 // iteration ahead, with the current pair's taps.
-__global__ void __launch_bounds__(256) k_prefilter(const Rgb *__restrict__ env, int S, int sm,
-                                                   const float4 *__restrict__ table, int samples,
-                                                   float4 *__restrict__ out) {
+__device__ __forceinline__ void prefilter_block(int block, int blocks, const Rgb *__restrict__ env, int S, int sm,
+                                                const float4 *__restrict__ table, int samples,
+                                                float4 *__restrict__ out) {
     int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // XCD-aware: each XCD's blocks take a contiguous run of texels, whose lobes
     // cover a fraction of the environment that its own L2 can hold
-    int o = xcd_tile((int)blockIdx.x, (int)gridDim.x) * 4 + wave;
+    int o = xcd_tile(block, blocks) * 4 + wave;
     if (o >= 6 * sm * sm) return;  // whole wavefront leaves together
     int f = o / (sm * sm), j = (o / sm) % sm, i = o % sm;
     v3 n = normalize(cube_texel_dir(f, i, j, sm));
@@ -385,15 +429,16 @@ __global__ void __launch_bounds__(256) k_prefilter(const Rgb *__restrict__ env, 
 // k's direction l is its half vector reflected about the texel normal n; with
 // N.L > 0 it adds L(l) N.L and N.L, L read trilinearly from the environment
 // chain at the sample's level.  part: [chunk][texel][8] = Kahan (s, c) of R,
-// G, B and the weight, as k_irradiance_final sums them.
-__global__ void __launch_bounds__(256) k_prefilter_fis(const float4 *__restrict__ chain, int S, int last, int sm,
-                                                       const float4 *__restrict__ table, int samples, int chunks,
-                                                       float *__restrict__ part) {
+// G, B and the weight, as irradiance_final_block sums them.
+__device__ __forceinline__ void prefilter_fis_block(int block, const float4 *__restrict__ env,
+                                                    const float4 *__restrict__ chain, int S, int last, int sm,
+                                                    const float4 *__restrict__ table, int samples, int chunks,
+                                                    float *__restrict__ part) {
     // wave-uniform by construction; readfirstlane tells the compiler, so the
     // sample loop and its table loads are scalar
     // (not XCD-aware: the matched mip levels are small enough for every L2,
     // and the XCD-contiguous order measured slower here)
-    int w = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
+    int w = __builtin_amdgcn_readfirstlane(block * 4 + (int)(threadIdx.x >> 6));
     int lane = threadIdx.x & 63;
     int tpf = (sm + 7) >> 3;
     if (w >= 6 * tpf * tpf * chunks) return;  // whole wavefront leaves together
@@ -413,14 +458,13 @@ __global__ void __launch_bounds__(256) k_prefilter_fis(const float4 *__restrict_
         v3 l = h * (2.0f * vh) - n;
         float nl = dot(n, l);
         if (nl > 0.0f) {
-            float lod = tk.w;
-            int l0 = (int)lod;
+            float lod = tk.w;  // the sample's, so wave-uniform
+            int l0 = __builtin_amdgcn_readfirstlane((int)lod);
             int l1 = min(l0 + 1, last);
             float fl = lod - (float)l0;
             FaceST fs = cube_face(l);
-            int s0 = S >> l0, s1 = S >> l1;
-            float4 L0 = face_bilinear(chain, chain_offset_pow2(S, l0), face_dims(s0), fs);
-            float4 L1 = face_bilinear(chain, chain_offset_pow2(S, l1), face_dims(s1), fs);
+            float4 L0 = face_bilinear(l0 ? chain + chain_offset_pow2(S, l0) : env, 0u, face_dims(S >> l0), fs);
+            float4 L1 = face_bilinear(l1 ? chain + chain_offset_pow2(S, l1) : env, 0u, face_dims(S >> l1), fs);
             float4 L = lerp4(L0, L1, fl);
             kahan_add(r, L.x * nl);
             kahan_add(g, L.y * nl);
@@ -476,10 +520,10 @@ __global__ void __launch_bounds__(256) k_brdf_lut(int size, int samples, float2 
 // the samples as in k_brdf_lut (the same order); G_vis from a reciprocal, the
 // compensated sums over groups of four samples.
 constexpr int kLutLdsSamples = 2048, kLutRowSlice = 32;
-__global__ void __launch_bounds__(256) k_brdf_lut_rows(int size, int samples, float2 *__restrict__ out) {
-    extern __shared__ float4 tab[];  // samples entries (launched with samples * 16 bytes)
+__device__ __forceinline__ void brdf_lut_rows_block(int block, int size, int samples, float2 *__restrict__ out,
+                                                    float4 *tab) {  // tab: samples entries in LDS
     int slices = (size + kLutRowSlice - 1) / kLutRowSlice;
-    int j = (int)blockIdx.x / slices, i0 = ((int)blockIdx.x - j * slices) * kLutRowSlice;
+    int j = block / slices, i0 = (block - j * slices) * kLutRowSlice;
     float rough = ((float)j + 0.5f) / (float)size;
     float alpha = rough * rough, a2 = alpha * alpha, k = 0.5f * alpha;
     float inv_n = 1.0f / (float)samples;
@@ -533,6 +577,126 @@ __global__ void __launch_bounds__(256) k_brdf_lut_rows(int size, int samples, fl
     }
 }
 
+// ---------------------------------------------------------------------------
+// launches
+// ---------------------------------------------------------------------------
+// Independent steps share a launch, each workgroup taking one step's block by its
+// index: (1) irradiance source, RGB copy or the first chain levels, GGX tables and
+// mirror levels; (chain levels beyond five: one launch per five more); (2) the
+// integrals (rough prefiltered levels, irradiance partials, BRDF table); (3) the
+// sums of partials.  Besides the launches this saves the tails of small levels,
+// and it runs the prefilter, which the texture data path bounds, beside the
+// irradiance and the BRDF table, which vector issue bounds.  One launch per step and
+// level (ten, with filtered sampling sixteen or more) took 544 us at 6x512^2 and
+// 108 us for the small filtered tables of a 6x64^2 cube, this takes 407 and 49; the
+// integral launch is 411 of the former against 511 of its steps one by one, with the
+// texture data path 89 % and vector issue 69 % busy.
+struct IblLevel {
+    int sm, chunks;         // face size; sample chunks (filtered sampling)
+    int blocks;             // blocks in the integral launch (padded to whole rounds of XCDs)
+    int final_blocks;       // blocks of the sum of partials
+    float *part;
+    const float4 *table;
+    float4 *out;
+};
+struct IblArgs {
+    const float4 *env;
+    int S, src, irr, lpt, chunks, chunk_len;
+    int fis, chain_last, levels, pref_samples, lut, lut_samples;
+    float4 *src_tex, *src_tab, *chain;
+    Rgb *rgb;
+    float *part;
+    float4 *ggx, *irr_out;
+    float2 *lut_out;
+    GgxLevels lv;
+    IblLevel level[8];
+    int source_blocks, env_blocks, ggx_blocks;   // launch 1 (then the mirror levels' blocks)
+    int heavy, light, heavy_run, light_run;      // launch 2: blocks of each kind, and of each in a round / 8
+    int partial_blocks, lut_blocks, out_blocks;  // (light = partial_blocks + lut_blocks)
+};
+
+template <bool kFis>
+__global__ void __launch_bounds__(256) k_ibl_prepare(const IblArgs a) {
+    int b = (int)blockIdx.x;
+    if (b < a.source_blocks) return ibl_source_block(b, a.env, a.S, a.src, a.lpt, a.src_tex, a.src_tab);
+    b -= a.source_blocks;
+    if (b < a.env_blocks) {
+        if constexpr (kFis) {
+            __shared__ ChainLds sm;
+            env_chain_block(b, a.env, a.chain, a.S, 0, a.chain_last, sm);
+        } else {
+            env_rgb_block(b, a.env, 6 * a.S * a.S, a.rgb);
+        }
+        return;
+    }
+    b -= a.env_blocks;
+    if (b < a.ggx_blocks) {
+        int per = (a.pref_samples + 255) / 256, m = b / per;
+        return ggx_table_block(b - m * per, m, a.lv, a.pref_samples, a.fis, a.chain_last, a.ggx);
+    }
+    b -= a.ggx_blocks;
+    for (int m = 0; m < a.levels; ++m) {
+        if (a.lv.alpha[m] != 0.0f) continue;
+        int n = (6 * a.level[m].sm * a.level[m].sm + 255) / 256;
+        if (b < n) return prefilter_mirror_block(b, a.env, a.S, a.level[m].sm, a.level[m].out);
+        b -= n;
+    }
+}
+
+__global__ void __launch_bounds__(256) k_env_chain(const IblArgs a, int first) {
+    __shared__ ChainLds sm;
+    env_chain_block((int)blockIdx.x, a.env, a.chain, a.S, first, a.chain_last, sm);
+}
+
+// Rounds of 8 heavy_run prefilter blocks and 8 light_run others: the two kinds are
+// spread evenly over the launch, and every index keeps its XCD (blockIdx % 8).
+template <bool kFis>
+__global__ void __launch_bounds__(256) k_ibl_integrate(const IblArgs a) {
+    extern __shared__ float4 lds[];
+    int run = kNumXcd * (a.heavy_run + a.light_run);
+    int round = (int)blockIdx.x / run, at = (int)blockIdx.x - round * run;
+    if (at < kNumXcd * a.heavy_run) {
+        int b = round * kNumXcd * a.heavy_run + at;
+        for (int m = 0; m < a.levels; ++m) {
+            const IblLevel &v = a.level[m];
+            if (b < v.blocks) {
+                if constexpr (kFis)
+                    prefilter_fis_block(b, a.env, a.chain, a.S, a.chain_last, v.sm, v.table, a.pref_samples, v.chunks,
+                                        v.part);
+                else
+                    prefilter_block(b, v.blocks, a.rgb, a.S, v.sm, v.table, a.pref_samples, v.out);
+                return;
+            }
+            b -= v.blocks;
+        }
+        return;
+    }
+    int b = round * kNumXcd * a.light_run + at - kNumXcd * a.heavy_run;
+    if (b < a.partial_blocks) {
+        int c = b / a.out_blocks;
+        return irradiance_partial_block(b - c * a.out_blocks, c, a.src_tex, a.src_tab, 6 * a.src * a.src, a.chunk_len,
+                                        a.irr, a.part, lds);
+    }
+    b -= a.partial_blocks;
+    if (b < a.lut_blocks) brdf_lut_rows_block(b, a.lut, a.lut_samples, a.lut_out, lds);
+}
+
+__global__ void __launch_bounds__(256) k_brdf_lut_rows(int size, int samples, float2 *__restrict__ out) {
+    extern __shared__ float4 lds[];
+    brdf_lut_rows_block((int)blockIdx.x, size, samples, out, lds);
+}
+
+__global__ void __launch_bounds__(256) k_ibl_final(const IblArgs a) {
+    int b = (int)blockIdx.x, nout = 6 * a.irr * a.irr, n = (4 * nout + 255) / 256;
+    if (b < n) return irradiance_final_block(b, a.part, a.chunks, nout, a.irr_out);
+    b -= n;
+    for (int m = 0; m < a.levels; ++m) {
+        const IblLevel &v = a.level[m];
+        if (b < v.final_blocks) return irradiance_final_block(b, v.part, v.chunks, 6 * v.sm * v.sm, v.out);
+        b -= v.final_blocks;
+    }
+}
+
 // Sample chunks of a prefiltered level of face size sm: enough wavefronts to
 // fill the chip (about 8192, 32 per CU) without splitting a tile's samples
 // more than 16 ways.
@@ -575,15 +739,13 @@ IblPlan ibl_plan(int S, const epb_ibl_params &p) {
     q.off_src = take((size_t)nsrc * 16);
     q.off_tab = take((size_t)nsrc * 16);
     q.off_part = take((size_t)chunks * nout * 8 * 4);
-    // environment mip chain for filtered importance sampling: levels 0 .. last
-    // contiguous, level k at texel offset 8 (S^2 - (S >> k)^2)
-    q.off_chain = take(q.fis ? (size_t)8 * S * S * 16 : 0);
-    // the prefilter's GGX sample table and partial sums, one level at a time
+    // environment mip chain for filtered importance sampling: levels 1 .. last
+    q.off_chain = take(q.fis ? (size_t)2 * S * S * 16 : 0);
+    // the prefilter's GGX sample tables and partial sums of every level
     size_t part = 0;
     for (int m = 1; q.fis && m < q.pref_levels; ++m) {  // (level 0 has roughness 0: no samples)
         int sm = q.pref_base >> m;
-        size_t need = (size_t)prefilter_chunks(sm) * 6 * sm * sm * 8 * 4;
-        if (need > part) part = need;
+        part += (size_t)prefilter_chunks(sm) * 6 * sm * sm * 8 * 4;
     }
     q.off_ggx = take(q.pref_levels > 1 ? (size_t)q.pref_levels * q.pref_samples * 16 : 0);  // a table per level
     q.off_rgb = take(!q.fis && q.pref_levels > 1 ? (size_t)6 * S * S * 12 : 0);  // level 0 as packed RGB
@@ -592,88 +754,98 @@ IblPlan ibl_plan(int S, const epb_ibl_params &p) {
     return q;
 }
 
+// Most LDS a block of the integral launch may take for the BRDF table's samples: at
+// 16 KB ten workgroups fit a CU, more than the prefilter's registers allow.
+constexpr int kLutSharedSamples = 1024;
+
 hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr, float *pref, float *lut,
                                  void *scratch, hipStream_t s) {
     char *sc = (char *)scratch;
-    float4 *src = (float4 *)(sc + q.off_src);
-    float4 *tab = (float4 *)(sc + q.off_tab);
-    float *part = (float *)(sc + q.off_part);
-    const float4 *env4 = (const float4 *)env;
-    int nsrc = 6 * q.src * q.src;
-    int nout = 6 * q.irr * q.irr;
-    int kk = (q.S / q.src) * (q.S / q.src), lpt = 1;
-    while (lpt < kk && lpt < 64) lpt *= 2;
-    long long threads = (long long)nsrc * lpt;
-    hipLaunchKernelGGL(k_ibl_source, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, env4, q.S, q.src,
-                       lpt, src, tab);
-    int chunk_len = (nsrc + q.chunks - 1) / q.chunks;
-    hipLaunchKernelGGL(k_irradiance_partial, dim3((nout + 255) / 256, q.chunks), dim3(256), 0, s, src, tab,
-                       nsrc, chunk_len, q.irr, part);
-    hipLaunchKernelGGL(k_irradiance_final, dim3((nout + 255) / 256), dim3(256), 0, s, part, q.chunks, q.irr,
-                       (float4 *)irr);
-    float4 *chain = (float4 *)(sc + q.off_chain);
-    float4 *ggx = (float4 *)(sc + q.off_ggx);
+    IblArgs a{};
+    a.env = (const float4 *)env;
+    a.S = q.S; a.src = q.src; a.irr = q.irr; a.chunks = q.chunks;
+    a.fis = q.fis; a.chain_last = q.chain_last; a.levels = q.pref_levels; a.pref_samples = q.pref_samples;
+    a.lut = q.lut; a.lut_samples = q.lut_samples;
+    a.src_tex = (float4 *)(sc + q.off_src);
+    a.src_tab = (float4 *)(sc + q.off_tab);
+    a.part = (float *)(sc + q.off_part);
+    a.chain = (float4 *)(sc + q.off_chain);
+    a.rgb = (Rgb *)(sc + q.off_rgb);
+    a.ggx = (float4 *)(sc + q.off_ggx);
+    a.irr_out = (float4 *)irr;
+    a.lut_out = (float2 *)lut;
+    int nsrc = 6 * q.src * q.src, nout = 6 * q.irr * q.irr, n0 = 6 * q.S * q.S;
+    int kk = (q.S / q.src) * (q.S / q.src);
+    a.lpt = 1;
+    while (a.lpt < kk && a.lpt < 64) a.lpt *= 2;
+    a.chunk_len = (nsrc + q.chunks - 1) / q.chunks;
+    // the levels, and the blocks of every step
     float *ppart = (float *)(sc + q.off_ppart);
-    if (q.fis) {
-        int n0 = 6 * q.S * q.S;
-        hipLaunchKernelGGL(k_env_copy, dim3((n0 + 255) / 256), dim3(256), 0, s, env4, n0, chain);
-        for (int k = 1; k <= q.chain_last; ++k) {
-            int Sd = q.S >> k;
-            hipLaunchKernelGGL(k_env_down, dim3((6 * Sd * Sd + 255) / 256), dim3(256), 0, s,
-                               (const float4 *)(chain + 8u * ((unsigned)q.S * q.S - (unsigned)(2 * Sd) * (2 * Sd))),
-                               2 * Sd, chain + 8u * ((unsigned)q.S * q.S - (unsigned)Sd * Sd));
-        }
-    }
-    GgxLevels lv{};
+    float4 *out = (float4 *)pref;
+    int mirror_blocks = 0, final_blocks = ceil_div(4 * nout, 256);
     for (int m = 0; m < q.pref_levels; ++m) {
+        IblLevel &v = a.level[m];
+        v.sm = q.pref_base >> m;
+        int n = 6 * v.sm * v.sm;
+        v.out = out;
+        out += n;
+        v.table = a.ggx + (size_t)m * q.pref_samples;
         float rough = q.pref_levels > 1 ? (float)m / (float)(q.pref_levels - 1) : 0.0f;
-        lv.alpha[m] = rough * rough;
-        if (q.fis && lv.alpha[m] != 0.0f) {
-            double a2 = (double)lv.alpha[m] * lv.alpha[m];
-            lv.lod0[m] = (float)(0.5 * std::log2(6.0 * q.S * q.S * a2 / q.pref_samples) + 1.0);
-        }
-    }
-    Rgb *rgb = (Rgb *)(sc + q.off_rgb);
-    if (!q.fis && q.pref_levels > 1) {
-        int n0 = 6 * q.S * q.S;
-        hipLaunchKernelGGL(k_env_rgb, dim3((n0 + 255) / 256), dim3(256), 0, s, env4, n0, rgb);
-    }
-    if (q.pref_levels > 1)
-        hipLaunchKernelGGL(k_ggx_table, dim3((q.pref_samples + 255) / 256, q.pref_levels), dim3(256), 0, s, lv,
-                           q.pref_samples, q.fis, q.chain_last, ggx);
-    size_t off = 0;
-    for (int m = 0; m < q.pref_levels; ++m) {
-        int sm = q.pref_base >> m;
-        float alpha = lv.alpha[m];
-        const float4 *table = ggx + (size_t)m * q.pref_samples;
-        int n = 6 * sm * sm;
-        float4 *dst = (float4 *)pref + off;
+        float alpha = a.lv.alpha[m] = rough * rough;
         if (alpha == 0.0f) {
-            hipLaunchKernelGGL(k_prefilter_mirror, dim3((n + 255) / 256), dim3(256), 0, s, env4, q.S, sm, dst);
-        } else {
-            // (stream order: the previous level's kernels are done with the partials)
-            if (q.fis) {
-                int chunks = prefilter_chunks(sm), tpf = (sm + 7) / 8;
-                int waves = 6 * tpf * tpf * chunks;
-                hipLaunchKernelGGL(k_prefilter_fis, dim3((waves + 3) / 4), dim3(256), 0, s, chain, q.S,
-                                   q.chain_last, sm, table, q.pref_samples, chunks, ppart);
-                hipLaunchKernelGGL(k_irradiance_final, dim3((n + 255) / 256), dim3(256), 0, s, ppart, chunks, sm,
-                                   dst);
-            } else {
-                hipLaunchKernelGGL(k_prefilter, dim3((n + 3) / 4), dim3(256), 0, s, (const Rgb *)rgb, q.S, sm,
-                                   table, q.pref_samples, dst);
-            }
+            mirror_blocks += ceil_div(n, 256);
+            continue;
         }
-        off += (size_t)n;
+        int blocks = ceil_div(n, 4);
+        if (q.fis) {
+            double a2 = (double)alpha * alpha;
+            a.lv.lod0[m] = (float)(0.5 * std::log2(6.0 * q.S * q.S * a2 / q.pref_samples) + 1.0);
+            int tpf = (v.sm + 7) / 8;
+            v.chunks = prefilter_chunks(v.sm);
+            v.part = ppart;
+            ppart += (size_t)v.chunks * n * 8;
+            v.final_blocks = ceil_div(4 * n, 256);
+            final_blocks += v.final_blocks;
+            blocks = ceil_div(6 * tpf * tpf * v.chunks, 4);
+        }
+        v.blocks = ceil_div(blocks, kNumXcd) * kNumXcd;
+        a.heavy += v.blocks;
     }
-    if (q.lut_samples <= kLutLdsSamples) {
-        int slices = (q.lut + kLutRowSlice - 1) / kLutRowSlice;
-        hipLaunchKernelGGL(k_brdf_lut_rows, dim3(q.lut * slices), dim3(256), (size_t)q.lut_samples * sizeof(float4), s,
-                           q.lut, q.lut_samples, (float2 *)lut);
-    } else {
-        int nl = q.lut * q.lut;
-        hipLaunchKernelGGL(k_brdf_lut, dim3((nl + 3) / 4), dim3(256), 0, s, q.lut, q.lut_samples, (float2 *)lut);
+    a.source_blocks = ceil_div(q.src * q.src * a.lpt, 256);
+    int side = q.S < 32 ? q.S : 32;
+    if (q.fis) a.env_blocks = q.chain_last > 0 ? (q.S / side) * (q.S / side) : 0;
+    else a.env_blocks = q.pref_levels > 1 ? ceil_div(n0, 256) : 0;
+    a.ggx_blocks = q.pref_levels > 1 ? ceil_div(q.pref_samples, 256) * q.pref_levels : 0;
+    a.out_blocks = ceil_div(nout, 256);
+    a.partial_blocks = a.out_blocks * q.chunks;
+    bool lut_shared = q.lut_samples <= kLutSharedSamples, lut_rows = q.lut_samples <= kLutLdsSamples;
+    int lut_blocks = q.lut * ceil_div(q.lut, kLutRowSlice);
+    a.lut_blocks = lut_shared ? lut_blocks : 0;
+    a.light = a.partial_blocks + a.lut_blocks;
+    // rounds of 8 prefilter blocks per XCD, the others spread over them
+    a.heavy_run = a.heavy > 0 ? 8 : 0;
+    int rounds = a.heavy > 0 ? ceil_div(a.heavy, kNumXcd * a.heavy_run) : 1;
+    a.light_run = ceil_div(a.light, kNumXcd * rounds);
+    int grid = rounds * kNumXcd * (a.heavy_run + a.light_run);
+    size_t lds = 2 * 256 * sizeof(float4);
+    if (lut_shared && (size_t)q.lut_samples * sizeof(float4) > lds) lds = (size_t)q.lut_samples * sizeof(float4);
+
+    int first = a.source_blocks + a.env_blocks + a.ggx_blocks + mirror_blocks;
+    if (q.fis) hipLaunchKernelGGL(k_ibl_prepare<true>, dim3(first), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_ibl_prepare<false>, dim3(first), dim3(256), 0, s, a);
+    for (int k = kChainStep; q.fis && k < q.chain_last; k += kChainStep) {
+        int Sk = q.S >> k, w = Sk < 32 ? 1 : Sk / 32;
+        hipLaunchKernelGGL(k_env_chain, dim3(w * w), dim3(256), 0, s, a, k);
     }
+    if (q.fis) hipLaunchKernelGGL(k_ibl_integrate<true>, dim3(grid), dim3(256), lds, s, a);
+    else hipLaunchKernelGGL(k_ibl_integrate<false>, dim3(grid), dim3(256), lds, s, a);
+    hipLaunchKernelGGL(k_ibl_final, dim3(final_blocks), dim3(256), 0, s, a);
+    if (!lut_shared && lut_rows)
+        hipLaunchKernelGGL(k_brdf_lut_rows, dim3(lut_blocks), dim3(256), (size_t)q.lut_samples * sizeof(float4), s,
+                           q.lut, q.lut_samples, a.lut_out);
+    else if (!lut_rows)
+        hipLaunchKernelGGL(k_brdf_lut, dim3(ceil_div(q.lut * q.lut, 4)), dim3(256), 0, s, q.lut, q.lut_samples,
+                           a.lut_out);
     return hipGetLastError();
 }
 
