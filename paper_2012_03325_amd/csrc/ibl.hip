@@ -18,8 +18,9 @@
 //    per-lane Kahan sums, compensated wave reduction through cross-lane
 //    shuffles; a lane takes two samples at a time (both lookups' taps in
 //    flight), their half vectors from the level's table one iteration ahead,
-//    the taps from a packed RGB copy of the environment (the texture data path
-//    bounds this kernel, and the fourth channel is never used).
+//    the taps from a copy of the environment that holds vertical pairs of RGB
+//    texels (the texture data path bounds this kernel: fewer loads and lines per
+//    lookup).
 //  * prefilter with filtered importance sampling (taps on the mip level that
 //    matches each sample's footprint): one wavefront per 8x8 tile of output
 //    texels and chunk of the samples; all lanes take the same sample at once,
@@ -245,12 +246,15 @@ __device__ __forceinline__ float4 mean_of_children(const float4 (&L)[4], const f
 }
 
 // Up to five chain levels in one launch: a block takes the 32 x 32 texels (or the
-// whole face) at its place of level `first` of all six faces (the solid angles do
-// not depend on the face) and writes what it covers of the levels below it, each
-// from the one before in LDS.
+// whole face) at its place of level `first` of all six faces and writes what it
+// covers of the levels below it, each from the one before in LDS.  The solid angles
+// of all its levels, which do not depend on the face, are made first, side by side
+// (level after level they are a serial chain: 17 us for the preparing launch of a
+// 6x64^2 cube).
 constexpr int kChainStep = 5;
 struct ChainLds {
     float4 a[6 * 16 * 16], b[6 * 8 * 8];
+    float dw[32 * 32 + 16 * 16 + 8 * 8 + 4 * 4 + 2 * 2];
 };
 __device__ __forceinline__ void env_chain_block(int block, const float4 *__restrict__ env, float4 *__restrict__ chain,
                                                 int S, int first, int last, ChainLds &sm) {
@@ -261,6 +265,16 @@ __device__ __forceinline__ void env_chain_block(int block, const float4 *__restr
     int by = block / across, bx = block - by * across;
     float4 *from = nullptr, *to = sm.a;
     int t = (int)threadIdx.x;
+    int levels = min(kChainStep, last - first), total = 0;
+    for (int r = 0; r < levels; ++r) total += (side >> r) * (side >> r);
+    for (int q = t; q < total; q += 256) {
+        int r = 0, e = q;
+        while (e >= (side >> r) * (side >> r)) e -= (side >> r) * (side >> r), ++r;
+        int w = side >> r, y = e / w;
+        sm.dw[q] = texel_solid_angle(bx * w + (e - y * w), by * w + y, Sp >> r);
+    }
+    __syncthreads();
+    const float *dws = sm.dw;  // of the level that the children are on
     for (int k = first + 1; k <= min(first + kChainStep, last); ++k) {
         int n = side >> (k - first), Sd = S >> k;  // this block's n x n texels of level k
         float4 *out = chain + chain_offset_pow2(S, k);
@@ -271,7 +285,7 @@ __device__ __forceinline__ void env_chain_block(int block, const float4 *__restr
             int i = bx * n + lx, j = by * n + ly;
             float dw[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) dw[c] = texel_solid_angle(2 * i + (c & 1), 2 * j + (c >> 1), 2 * Sd);
+            for (int c = 0; c < 4; ++c) dw[c] = dws[(2 * ly + (c >> 1)) * 2 * n + 2 * lx + (c & 1)];
             for (int e = 0; e < each; ++e) {
                 int f = f0 + e;
                 float4 L[4];
@@ -287,33 +301,38 @@ __device__ __forceinline__ void env_chain_block(int block, const float4 *__restr
         __syncthreads();
         from = to;
         to = to == sm.a ? sm.b : sm.a;
+        dws += 4 * n * n;
         // (the next level's texels fit the other array: 6 n^2 / 4 of them; it is read no more)
     }
 }
 
-// Level 0 of the environment as packed RGB texels (12 bytes) for the
-// prefilter, whose taps use only the colour: each tap then moves three quarters
-// of the bytes through the texture data path, the unit that bounds it.
+// Level 0 of the environment for the prefilter, whose taps use only the colour: each
+// texel holds its own RGB and that of the texel below it (24 bytes; the last row
+// repeats itself and is never a lookup's upper row), so that the 2x2 texels of a
+// lookup are 48 bytes in one piece: three loads and mostly one cache line, where
+// rows of packed RGB took four loads and two lines (6x512^2 precompute: 407 us).
 struct Rgb {
     float r, g, b;
 };
-__device__ __forceinline__ void env_rgb_block(int block, const float4 *__restrict__ env, int n,
-                                              Rgb *__restrict__ dst) {
+struct RgbPair {
+    Rgb top, bottom;
+};
+__device__ __forceinline__ void env_rgb_block(int block, const float4 *__restrict__ env, int S,
+                                              RgbPair *__restrict__ dst) {
     int o = block * 256 + (int)threadIdx.x;
-    if (o < n) {
-        float4 v = env[o];
-        sto(dst, (unsigned)o * 12u, Rgb{v.x, v.y, v.z});
-    }
+    if (o >= 6 * S * S) return;
+    float4 t = env[o], u = env[o / S % S + 1 < S ? o + S : o];
+    sto(dst, (unsigned)o * 24u, RgbPair{Rgb{t.x, t.y, t.z}, Rgb{u.x, u.y, u.z}});
 }
 
-// face_bilinear over packed RGB texels, split into its loads and its
-// interpolation (so that a caller can have several lookups' loads in flight):
-// the same coordinates, taps and interpolation, so the same values.
+// face_bilinear over these texels, split into its loads and its interpolation (so
+// that a caller can have several lookups' loads in flight): the same coordinates,
+// taps and interpolation, so the same values.
 struct RgbTaps {
-    Rgb a, b, c, d;
+    float4 v[3];  // a.rgb c.r | c.gb b.rg | b.b d.rgb
     float wx, wy;
 };
-__device__ __forceinline__ RgbTaps rgb_taps(const Rgb *__restrict__ lvl, const FaceDims &g, FaceST f) {
+__device__ __forceinline__ RgbTaps rgb_taps(const RgbPair *__restrict__ lvl, const FaceDims &g, FaceST f) {
     RgbTaps q;
     float x = clamp_to(fmaf(f.s, g.half, g.off), g.hi);
     float y = clamp_to(fmaf(f.t, g.half, g.off), g.hi);
@@ -321,16 +340,14 @@ __device__ __forceinline__ RgbTaps rgb_taps(const Rgb *__restrict__ lvl, const F
     q.wx = x - x0f;
     q.wy = y - y0f;
     unsigned idx = __umul24((unsigned)fmaf(f.face, (float)g.S, y0f), (unsigned)g.S) + (unsigned)x0f;
-    unsigned o0 = idx * 12u, o1 = o0 + (unsigned)g.S * 12u;
-    q.a = ldo(lvl, o0);
-    q.b = ldo(lvl + 1, o0);
-    q.c = ldo(lvl, o1);
-    q.d = ldo(lvl + 1, o1);
+    const float4 *p = reinterpret_cast<const float4 *>(lvl);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) q.v[k] = ldo(p + k, idx * 24u);
     return q;
 }
 __device__ __forceinline__ float4 rgb_bilinear(const RgbTaps &q) {
-    float4 A = make_float4(q.a.r, q.a.g, q.a.b, 0.0f), B = make_float4(q.b.r, q.b.g, q.b.b, 0.0f);
-    float4 C = make_float4(q.c.r, q.c.g, q.c.b, 0.0f), D = make_float4(q.d.r, q.d.g, q.d.b, 0.0f);
+    float4 A = make_float4(q.v[0].x, q.v[0].y, q.v[0].z, 0.0f), C = make_float4(q.v[0].w, q.v[1].x, q.v[1].y, 0.0f);
+    float4 B = make_float4(q.v[1].z, q.v[1].w, q.v[2].x, 0.0f), D = make_float4(q.v[2].y, q.v[2].z, q.v[2].w, 0.0f);
     return lerp4(lerp4(A, B, q.wx), lerp4(C, D, q.wx), q.wy);
 }
 
@@ -362,13 +379,13 @@ __device__ __forceinline__ void ggx_table_block(int block, int m, const GgxLevel
 }
 
 // One wavefront per prefiltered texel of a level (roughness > 0), from level 0
-// of the environment (its packed RGB copy): sample k's half vector from the table, its direction l
+// of the environment (its RGB pairs): sample k's half vector from the table, its direction l
 // the half vector reflected about the texel normal n; with N.L > 0 it adds
 // L(l) N.L and N.L.  A lane takes its samples k and k + 64 together: both
 // lookups' taps are in flight before either is added (the adds keep the order
 // k, k + 64, k + 128, ...), and the next pair's table entries load one
 // iteration ahead, with the current pair's taps.
-__device__ __forceinline__ void prefilter_block(int block, int blocks, const Rgb *__restrict__ env, int S, int sm,
+__device__ __forceinline__ void prefilter_block(int block, int blocks, const RgbPair *__restrict__ env, int S, int sm,
                                                 const float4 *__restrict__ table, int samples,
                                                 float4 *__restrict__ out) {
     int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -518,35 +535,38 @@ __global__ void __launch_bounds__(256) k_brdf_lut(int size, int samples, float2 
 // to kLutLdsSamples samples): block b takes kLutRowSlice entries of one row (one
 // roughness), each wavefront a quarter of them in turn, its lanes splitting
 // the samples as in k_brdf_lut (the same order); G_vis from a reciprocal, the
-// compensated sums over groups of four samples.
+// compensated sums over groups of four samples.  The tangent frame of n = +z is
+// T = -y, B = +x, so a half vector (x, y, z) of the sample table is (y, -x, z) in
+// the frame of V, which has no y component: the table keeps (y, z), 8 bytes a
+// sample, and V.h is two products (the table alone: 67 us with the frame's nine).
 constexpr int kLutLdsSamples = 2048, kLutRowSlice = 32;
 __device__ __forceinline__ void brdf_lut_rows_block(int block, int size, int samples, float2 *__restrict__ out,
-                                                    float4 *tab) {  // tab: samples entries in LDS
+                                                    float2 *tab) {  // tab: samples entries in LDS
     int slices = (size + kLutRowSlice - 1) / kLutRowSlice;
     int j = block / slices, i0 = (block - j * slices) * kLutRowSlice;
     float rough = ((float)j + 0.5f) / (float)size;
     float alpha = rough * rough, a2 = alpha * alpha, k = 0.5f * alpha;
     float inv_n = 1.0f / (float)samples;
-    for (int s = (int)threadIdx.x; s < samples; s += 256)
-        tab[s] = ggx_tangent((float)s * inv_n, radical_inverse2((uint32_t)s), a2);
+    for (int s = (int)threadIdx.x; s < samples; s += 256) {
+        float4 t = ggx_tangent((float)s * inv_n, radical_inverse2((uint32_t)s), a2);
+        tab[s] = make_float2(t.y, t.z);
+    }
     __syncthreads();
     int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    v3 n = mk3(0.0f, 0.0f, 1.0f), T, B;
-    tangent_frame(n, T, B);
     for (int q = wave; q < kLutRowSlice; q += 4) {
         int i = i0 + q;
         if (i >= size) break;  // wave-uniform
         float NoV = ((float)i + 0.5f) / (float)size;
-        v3 V = mk3(sqrtf(fmaxf(0.0f, 1.0f - NoV * NoV)), 0.0f, NoV);
+        float Vx = sqrtf(fmaxf(0.0f, 1.0f - NoV * NoV));
         float gv = fmaf(NoV, 1.0f - k, k);
         // Sample s's two terms, both >= 0: with N.L clamped at 0, a sample
         // below the horizon gets G_vis = 0 (N.L is a factor, the denominator
         // stays positive: h.z > 0, k > 0) and adds nothing, as if skipped.
         auto terms = [&](int s, float &ta, float &tb) {
-            v3 h = ggx_to_world(tab[s], n, T, B);
-            float vh = dot(V, h);
-            float nl = fmaxf(fmaf(2.0f * vh, h.z, -V.z), 0.0f);
-            float gvis = nl * vh * rcp(h.z * fmaf(nl, 1.0f - k, k) * gv);
+            float2 h = tab[s];
+            float vh = fmaf(Vx, h.x, NoV * h.y);
+            float nl = fmaxf(fmaf(2.0f * vh, h.y, -NoV), 0.0f);
+            float gvis = nl * vh * rcp(h.y * fmaf(nl, 1.0f - k, k) * gv);
             float fc = pow5(1.0f - vh);
             ta = (1.0f - fc) * gvis;
             tb = fc * gvis;
@@ -588,9 +608,10 @@ __device__ __forceinline__ void brdf_lut_rows_block(int block, int size, int sam
 // and it runs the prefilter, which the texture data path bounds, beside the
 // irradiance and the BRDF table, which vector issue bounds.  One launch per step and
 // level (ten, with filtered sampling sixteen or more) took 544 us at 6x512^2 and
-// 108 us for the small filtered tables of a 6x64^2 cube, this takes 407 and 49; the
-// integral launch is 411 of the former against 511 of its steps one by one, with the
-// texture data path 89 % and vector issue 69 % busy.
+// 108 us for the small filtered tables of a 6x64^2 cube, this takes 348 and 43.  At
+// 6x512^2 the preparing launch is 28 us (25 MB read, 38 MB written), the integrals 345
+// (its steps one by one, with row-wise packed texels: 511), bound by vector issue (82 %
+// busy) and the texture data path (89 %), the sums 6.
 struct IblLevel {
     int sm, chunks;         // face size; sample chunks (filtered sampling)
     int blocks;             // blocks in the integral launch (padded to whole rounds of XCDs)
@@ -604,7 +625,7 @@ struct IblArgs {
     int S, src, irr, lpt, chunks, chunk_len;
     int fis, chain_last, levels, pref_samples, lut, lut_samples;
     float4 *src_tex, *src_tab, *chain;
-    Rgb *rgb;
+    RgbPair *rgb;
     float *part;
     float4 *ggx, *irr_out;
     float2 *lut_out;
@@ -625,7 +646,7 @@ __global__ void __launch_bounds__(256) k_ibl_prepare(const IblArgs a) {
             __shared__ ChainLds sm;
             env_chain_block(b, a.env, a.chain, a.S, 0, a.chain_last, sm);
         } else {
-            env_rgb_block(b, a.env, 6 * a.S * a.S, a.rgb);
+            env_rgb_block(b, a.env, a.S, a.rgb);
         }
         return;
     }
@@ -678,12 +699,7 @@ __global__ void __launch_bounds__(256) k_ibl_integrate(const IblArgs a) {
                                         a.irr, a.part, lds);
     }
     b -= a.partial_blocks;
-    if (b < a.lut_blocks) brdf_lut_rows_block(b, a.lut, a.lut_samples, a.lut_out, lds);
-}
-
-__global__ void __launch_bounds__(256) k_brdf_lut_rows(int size, int samples, float2 *__restrict__ out) {
-    extern __shared__ float4 lds[];
-    brdf_lut_rows_block((int)blockIdx.x, size, samples, out, lds);
+    if (b < a.lut_blocks) brdf_lut_rows_block(b, a.lut, a.lut_samples, a.lut_out, (float2 *)lds);
 }
 
 __global__ void __launch_bounds__(256) k_ibl_final(const IblArgs a) {
@@ -748,15 +764,11 @@ IblPlan ibl_plan(int S, const epb_ibl_params &p) {
         part += (size_t)prefilter_chunks(sm) * 6 * sm * sm * 8 * 4;
     }
     q.off_ggx = take(q.pref_levels > 1 ? (size_t)q.pref_levels * q.pref_samples * 16 : 0);  // a table per level
-    q.off_rgb = take(!q.fis && q.pref_levels > 1 ? (size_t)6 * S * S * 12 : 0);  // level 0 as packed RGB
+    q.off_rgb = take(!q.fis && q.pref_levels > 1 ? (size_t)6 * S * S * sizeof(RgbPair) : 0);
     q.off_ppart = take(part);
     q.bytes = off;
     return q;
 }
-
-// Most LDS a block of the integral launch may take for the BRDF table's samples: at
-// 16 KB ten workgroups fit a CU, more than the prefilter's registers allow.
-constexpr int kLutSharedSamples = 1024;
 
 hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr, float *pref, float *lut,
                                  void *scratch, hipStream_t s) {
@@ -770,7 +782,7 @@ hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr,
     a.src_tab = (float4 *)(sc + q.off_tab);
     a.part = (float *)(sc + q.off_part);
     a.chain = (float4 *)(sc + q.off_chain);
-    a.rgb = (Rgb *)(sc + q.off_rgb);
+    a.rgb = (RgbPair *)(sc + q.off_rgb);
     a.ggx = (float4 *)(sc + q.off_ggx);
     a.irr_out = (float4 *)irr;
     a.lut_out = (float2 *)lut;
@@ -818,17 +830,17 @@ hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr,
     a.ggx_blocks = q.pref_levels > 1 ? ceil_div(q.pref_samples, 256) * q.pref_levels : 0;
     a.out_blocks = ceil_div(nout, 256);
     a.partial_blocks = a.out_blocks * q.chunks;
-    bool lut_shared = q.lut_samples <= kLutSharedSamples, lut_rows = q.lut_samples <= kLutLdsSamples;
-    int lut_blocks = q.lut * ceil_div(q.lut, kLutRowSlice);
-    a.lut_blocks = lut_shared ? lut_blocks : 0;
+    bool lut_rows = q.lut_samples <= kLutLdsSamples;
+    a.lut_blocks = lut_rows ? q.lut * ceil_div(q.lut, kLutRowSlice) : 0;
     a.light = a.partial_blocks + a.lut_blocks;
     // rounds of 8 prefilter blocks per XCD, the others spread over them
     a.heavy_run = a.heavy > 0 ? 8 : 0;
     int rounds = a.heavy > 0 ? ceil_div(a.heavy, kNumXcd * a.heavy_run) : 1;
     a.light_run = ceil_div(a.light, kNumXcd * rounds);
     int grid = rounds * kNumXcd * (a.heavy_run + a.light_run);
+    // (at most 16 KB: ten workgroups would fit a CU, more than the prefilter's registers allow)
     size_t lds = 2 * 256 * sizeof(float4);
-    if (lut_shared && (size_t)q.lut_samples * sizeof(float4) > lds) lds = (size_t)q.lut_samples * sizeof(float4);
+    if (lut_rows && (size_t)q.lut_samples * sizeof(float2) > lds) lds = (size_t)q.lut_samples * sizeof(float2);
 
     int first = a.source_blocks + a.env_blocks + a.ggx_blocks + mirror_blocks;
     if (q.fis) hipLaunchKernelGGL(k_ibl_prepare<true>, dim3(first), dim3(256), 0, s, a);
@@ -840,10 +852,7 @@ hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr,
     if (q.fis) hipLaunchKernelGGL(k_ibl_integrate<true>, dim3(grid), dim3(256), lds, s, a);
     else hipLaunchKernelGGL(k_ibl_integrate<false>, dim3(grid), dim3(256), lds, s, a);
     hipLaunchKernelGGL(k_ibl_final, dim3(final_blocks), dim3(256), 0, s, a);
-    if (!lut_shared && lut_rows)
-        hipLaunchKernelGGL(k_brdf_lut_rows, dim3(lut_blocks), dim3(256), (size_t)q.lut_samples * sizeof(float4), s,
-                           q.lut, q.lut_samples, a.lut_out);
-    else if (!lut_rows)
+    if (!lut_rows)
         hipLaunchKernelGGL(k_brdf_lut, dim3(ceil_div(q.lut * q.lut, 4)), dim3(256), 0, s, q.lut, q.lut_samples,
                            a.lut_out);
     return hipGetLastError();
