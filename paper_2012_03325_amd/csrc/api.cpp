@@ -469,9 +469,15 @@ int epb_shade_post(const epb_gbuffer *gbuf, const epb_camera *cam, const void *a
     epb::PostDesc d;
     if ((st = build_post(hdr_out, hdr_dtype, cam->width, cam->height, params, ldr_out, scratch, scratch_bytes, &d)))
         return st;
-    hipError_t e = epb::launch_shade(a, stream, &d);
+    // Level 1 in the shading pass saves reading the HDR image back, at about 60 vector instructions
+    // a wavefront in a pass that vector issue bounds.  That pays while launches and latency count
+    // (shading and post-processing, level 1 apart against in the pass: 1280x720 FP32 42.2 / 41.3 us,
+    // 1920x1080 FP32 79.4 / 77.7, FP16 65.8 / 66.5; 2560x1440 FP32 124.1 / 123.4, FP16 112.0 / 113.3)
+    // and costs on large images (3840x2160 FP32 251.8 / 253.4, FP16 227.1 / 236.8).
+    const bool in_pass = d.nl >= 1 && (size_t)cam->width * cam->height <= (size_t)3 << 20;
+    hipError_t e = epb::launch_shade(a, stream, in_pass ? &d : nullptr);
     if (e != hipSuccess) return hip_status(e);
-    return hip_status(epb::launch_bloom_tonemap(d, hdr_dtype, params->pyr_dtype, stream, d.nl >= 1));
+    return hip_status(epb::launch_bloom_tonemap(d, hdr_dtype, params->pyr_dtype, stream, in_pass));
 }
 
 size_t epb_batch_table_bytes(int32_t n_views) {
