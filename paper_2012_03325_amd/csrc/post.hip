@@ -46,8 +46,8 @@ __global__ void __launch_bounds__(256) k_bloom_blur(const PostDesc c) {
 }
 
 template <typename TH, typename TP>
-__global__ void __launch_bounds__(kPostTx) __attribute__((amdgpu_waves_per_eu(5))) k_composite(const PostDesc c, int tiles) {
-    composite_tile<TH, TP>(c, xcd_tile(blockIdx.x, tiles), (int)threadIdx.x);
+__global__ void __launch_bounds__(kPostTx) __attribute__((amdgpu_waves_per_eu(4))) k_composite(const PostDesc c, int tiles) {
+    composite_tile<sizeof(TP) == 8, TH, TP>(c, xcd_tile(blockIdx.x, tiles), (int)threadIdx.x);
 }
 
 template <typename TH, typename TP>
@@ -93,7 +93,7 @@ __global__ void __launch_bounds__(256) k_bloom_blur_batch(const void *__restrict
 }
 
 template <typename TH, typename TP>
-__global__ void __launch_bounds__(kPostTx) __attribute__((amdgpu_waves_per_eu(5))) k_composite_batch(const void *__restrict__ table) {
+__global__ void __launch_bounds__(kPostTx) __attribute__((amdgpu_waves_per_eu(4))) k_composite_batch(const void *__restrict__ table) {
     const BatchHeader *h = (const BatchHeader *)table;
     const int *start = batch_start(table, kStComposite);
     const ViewDesc *views = batch_views(table);
@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(kPostTx) __attribute__((amdgpu_waves_per_eu(5)
     for (int it = w.lb; it < w.count; it += w.stride) {
         int g = w.first + it;
         int v = find_view(start, h->n_views, g);
-        composite_tile<TH, TP>(views[v].post, g - start[v], (int)threadIdx.x);
+        composite_tile<sizeof(TP) == 8, TH, TP>(views[v].post, g - start[v], (int)threadIdx.x);
     }
 }
 

@@ -249,7 +249,7 @@ __device__ __forceinline__ uint32_t encode8(float x, float exposure, float inv_g
 // strip lies inside one texel row pair and the remainder grows by 2 per pixel
 // without wrapping); the weights of levels 1..3 are compile-time constants as
 // well.  Everything stays in registers: no LDS, no barriers, and the strip's
-// 24 HDR loads are in flight while the pyramid is read.  Rows are scalar addresses
+// 24 HDR loads are in flight with the pyramid's.  Rows are scalar addresses
 // and bytes are packed by their conversion, since vector issue bounds the batched
 // composite (81 % busy, half storage): 16 views of 13.2 Mpx 57 -> 52.5 us, and
 // bloom and tone mapping of 3840x2160 in half storage 63.8 -> 61.8 us, against
@@ -282,33 +282,41 @@ __device__ __forceinline__ float4 texel_difference(Half4 b, Half4 a) {
     return d;
 }
 
-// The level-L rows under the strip, interpolated at the thread's column.
+// The level-L texels beside the thread's column on the rows under the strip, and
+// the column's weight.
 template <int L, typename TP>
-__device__ __forceinline__ void level_rows(const PostDesc &c, int x, int Y0, float (&rows)[LevelRows<L>::n][3]) {
+struct LevelTexels {
+    TP a[LevelRows<L>::n], b[LevelRows<L>::n];
+    float wx;
+};
+template <int L, typename TP>
+__device__ __forceinline__ void load_level(const PostDesc &c, int x, int Y0, LevelTexels<L, TP> &t) {
     using LR = LevelRows<L>;
     const int w = c.lw[L], h = c.lh[L];
     const TP *lvl = (const TP *)c.blur[L];
     int vx = 2 * x + LR::o;
-    float wx = (float)(vx & LR::m) * LR::inv;
+    t.wx = (float)(vx & LR::m) * LR::inv;
     int cx = vx >> LR::sh;
     unsigned c0 = (unsigned)min(max(cx, 0), w - 1), c1 = (unsigned)min(max(cx + 1, 0), w - 1);
     unsigned o0 = c0 * (unsigned)sizeof(TP), o1 = c1 * (unsigned)sizeof(TP);
     int ay = (2 * Y0 + LR::o) >> LR::sh;
-    // all the level's texel loads issued before any is used (one memory round trip per level)
-    TP ta[LR::n], tb[LR::n];
 #pragma unroll
     for (int r = 0; r < LR::n; ++r) {
         const TP *row = lvl + (unsigned)min(max(ay + r, 0), h - 1) * (unsigned)w;  // uniform: scalar arithmetic
-        ta[r] = ldo(row, o0);
-        tb[r] = ldo(row, o1);
+        t.a[r] = ldo(row, o0);
+        t.b[r] = ldo(row, o1);
     }
-    __builtin_amdgcn_sched_barrier(0);  // keep the scheduler from interleaving the loads with their uses
+}
+
+// Their values interpolated at the thread's column.
+template <int L, typename TP>
+__device__ __forceinline__ void level_rows(const LevelTexels<L, TP> &t, float (&rows)[LevelRows<L>::n][3]) {
 #pragma unroll
-    for (int r = 0; r < LR::n; ++r) {
-        float4 a = unpack(ta[r]), d = texel_difference(tb[r], ta[r]);
-        rows[r][0] = fmaf(wx, d.x, a.x);
-        rows[r][1] = fmaf(wx, d.y, a.y);
-        rows[r][2] = fmaf(wx, d.z, a.z);
+    for (int r = 0; r < LevelRows<L>::n; ++r) {
+        float4 a = unpack(t.a[r]), d = texel_difference(t.b[r], t.a[r]);
+        rows[r][0] = fmaf(t.wx, d.x, a.x);
+        rows[r][1] = fmaf(t.wx, d.y, a.y);
+        rows[r][2] = fmaf(t.wx, d.z, a.z);
     }
 }
 
@@ -318,12 +326,13 @@ __device__ __forceinline__ void level_rows(const PostDesc &c, int x, int Y0, flo
 // enter as the first addend, so a pixel spends one FMA per level and channel.
 // Absent levels contribute nothing (their difference and weight are 0).
 template <typename TP>
-__device__ __forceinline__ void init_coarse(const PostDesc &c, int x, int Y0, float (&acc)[kPostTy][3]) {
+__device__ __forceinline__ void init_coarse(const PostDesc &c, int Y0, const LevelTexels<4, TP> &t4,
+                                            const LevelTexels<5, TP> &t5, float (&acc)[kPostTy][3]) {
     float base[3] = {0.0f, 0.0f, 0.0f}, d4[3] = {0.0f, 0.0f, 0.0f}, d5[3] = {0.0f, 0.0f, 0.0f};
     float w4 = 0.0f, w5 = 0.0f;
     if (c.nl >= 4) {
         float rows[2][3];
-        level_rows<4, TP>(c, x, Y0, rows);
+        level_rows<4, TP>(t4, rows);
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) {
             base[ch] = rows[0][ch];
@@ -333,7 +342,7 @@ __device__ __forceinline__ void init_coarse(const PostDesc &c, int x, int Y0, fl
     }
     if (c.nl >= 5) {
         float rows[2][3];
-        level_rows<5, TP>(c, x, Y0, rows);
+        level_rows<5, TP>(t5, rows);
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) {
             base[ch] += rows[0][ch];
@@ -351,10 +360,10 @@ __device__ __forceinline__ void init_coarse(const PostDesc &c, int x, int Y0, fl
 
 // Levels 1..3: (1 - w) a + w b for the pixel's row pair, two FMAs per channel.
 template <int L, typename TP>
-__device__ __forceinline__ void add_fine(const PostDesc &c, int x, int Y0, float (&acc)[kPostTy][3]) {
+__device__ __forceinline__ void add_fine(const LevelTexels<L, TP> &t, float (&acc)[kPostTy][3]) {
     using LR = LevelRows<L>;
     float rows[LR::n][3];
-    level_rows<L, TP>(c, x, Y0, rows);
+    level_rows<L, TP>(t, rows);
 #pragma unroll
     for (int j = 0; j < kPostTy; ++j) {
         const int r0 = LR::rel(j);
@@ -382,7 +391,7 @@ __device__ __forceinline__ void store_strip(const PostDesc &c, int x, int Y0, co
 }
 
 // One 64 x 8 tile by one wavefront; `lane` is the thread's lane (its column).
-template <typename TH, typename TP>
+template <bool kOneTrip, typename TH, typename TP>
 __device__ __forceinline__ void composite_tile(const PostDesc &c, int tile, int lane) {
     tile = __builtin_amdgcn_readfirstlane(tile);  // one per wavefront: rows are scalar addresses
     int tiles_x = (c.W + kPostTx - 1) / kPostTx;
@@ -402,12 +411,35 @@ __device__ __forceinline__ void composite_tile(const PostDesc &c, int tile, int 
         px[j][2] = ldf(row + 2 * (size_t)plane, (unsigned)x);
     }
     // the bloom sum of levels 5, 4 (one row pair for the whole strip), then 1 .. 3
-    // (nl is uniform)
+    // (nl is uniform).  The texels come in as few round trips as the registers hold:
+    // half texels all with the HDR (111 registers), float texels as {5, 4, 1} with it and
+    // {2, 3} (107; the scheduler would otherwise interleave loads and uses).  Four waves
+    // per SIMD are about what 1920x1080 has to give.  One trip per level: bloom and tone
+    // mapping of 1920x1080 float 26.8 us against 26.3, of 3840x2160 half 61.8 against
+    // 58.9; float texels in one trip need 140 registers (26.7).
     float acc[kPostTy][3];
-    init_coarse<TP>(c, x, Y0, acc);
-    if (c.nl >= 1) add_fine<1, TP>(c, x, Y0, acc);
-    if (c.nl >= 2) add_fine<2, TP>(c, x, Y0, acc);
-    if (c.nl >= 3) add_fine<3, TP>(c, x, Y0, acc);
+    LevelTexels<4, TP> t4;
+    LevelTexels<5, TP> t5;
+    LevelTexels<1, TP> t1;
+    LevelTexels<2, TP> t2;
+    LevelTexels<3, TP> t3;
+    if (c.nl >= 5) load_level<5, TP>(c, x, Y0, t5);
+    if (c.nl >= 4) load_level<4, TP>(c, x, Y0, t4);
+    if (c.nl >= 1) load_level<1, TP>(c, x, Y0, t1);
+    if (kOneTrip) {
+        if (c.nl >= 2) load_level<2, TP>(c, x, Y0, t2);
+        if (c.nl >= 3) load_level<3, TP>(c, x, Y0, t3);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    init_coarse<TP>(c, Y0, t4, t5, acc);
+    if (c.nl >= 1) add_fine<1, TP>(t1, acc);
+    if (!kOneTrip) {
+        if (c.nl >= 2) load_level<2, TP>(c, x, Y0, t2);
+        if (c.nl >= 3) load_level<3, TP>(c, x, Y0, t3);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (c.nl >= 2) add_fine<2, TP>(t2, acc);
+    if (c.nl >= 3) add_fine<3, TP>(t3, acc);
     if (c.tonemap == EPB_TONEMAP_REINHARD) store_strip<true>(c, x, Y0, px, acc);
     else store_strip<false>(c, x, Y0, px, acc);
 }
