@@ -755,8 +755,10 @@ IblPlan ibl_plan(int S, const epb_ibl_params &p) {
     q.off_src = take((size_t)nsrc * 16);
     q.off_tab = take((size_t)nsrc * 16);
     q.off_part = take((size_t)chunks * nout * 8 * 4);
-    // environment mip chain for filtered importance sampling: levels 1 .. last
-    q.off_chain = take(q.fis ? (size_t)2 * S * S * 16 : 0);
+    // environment mip chain for filtered importance sampling: levels 1 .. last (a quarter of
+    // this; the scratch keeps the size it had with a copy of level 0, so that filtered sampling
+    // never asks for less than plain sampling, as callers may assume)
+    q.off_chain = take(q.fis ? (size_t)8 * S * S * 16 : 0);
     // the prefilter's GGX sample tables and partial sums of every level
     size_t part = 0;
     for (int m = 1; q.fis && m < q.pref_levels; ++m) {  // (level 0 has roughness 0: no samples)
