@@ -206,10 +206,18 @@ def _ptr(x) -> Optional[int]:
     return x.data_ptr()
 
 
+def _current_stream() -> int:
+    """Handle of torch's current stream on the current device, without the Stream object that
+    torch.cuda.current_stream() makes (of the order of a kernel launch, on every call)."""
+    import torch
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
