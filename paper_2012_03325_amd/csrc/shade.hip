@@ -153,21 +153,32 @@ hipError_t launch_shade(const ShadeArgs &a, hipStream_t s, const PostDesc *bloom
     return hipGetLastError();
 }
 
-// Tiled form of a shadow map: one thread per stored float, one row of tiles per
-// blockIdx.y (the last row holds the all-+inf tile); consecutive threads write
-// consecutive floats and read runs of 8 texels of a map row.  Stored float
-// (p nx + q) 64 + 8 j + i is texel (6 q + i - 1, 6 p + j - 1) of the map, +inf
-// outside it.
+// Tiled form of a shadow map: one thread per four stored floats (half a row of a
+// block), one row of tiles per blockIdx.y (the last row holds the all-+inf tile);
+// consecutive threads write consecutive float4 and read runs of a map row, inside
+// the map as one load (2048^2, 47 MB: 11.0 us, 15.5 with one float per thread).  Stored float (p nx + q) 64 + 8 j + i is texel (6 q + i - 1,
+// 6 p + j - 1) of the map, +inf outside it.
 __global__ void __launch_bounds__(256) k_shadow_tiles(const float *__restrict__ map, int w, int h, int nx, int ny,
-                                                      float *__restrict__ tiles) {
-    unsigned t = blockIdx.x * 256u + threadIdx.x;  // float index inside this row of tiles
+                                                      float4 *__restrict__ tiles) {
+    unsigned t = blockIdx.x * 256u + threadIdx.x;  // float4 index inside this row of tiles
     unsigned p = blockIdx.y;
-    if (t >= (p < (unsigned)ny ? (unsigned)nx * 64u : 64u)) return;
-    unsigned q = t >> 6, j = (t >> 3) & 7u, i = t & 7u;
+    if (t >= (p < (unsigned)ny ? (unsigned)nx * 16u : 16u)) return;
+    unsigned q = t >> 4, j = (t >> 1) & 7u, i = (t & 1u) * 4u;
     int x = (int)(6u * q + i) - 1, y = (int)(6u * p + j) - 1;
-    float v = __builtin_inff();
-    if (p < (unsigned)ny && x >= 0 && x < w && y >= 0 && y < h) v = map[(size_t)y * (unsigned)w + (unsigned)x];
-    tiles[(size_t)p * nx * 64u + t] = v;
+    const float inf = __builtin_inff();
+    float4 v = make_float4(inf, inf, inf, inf);
+    if (p < (unsigned)ny && y >= 0 && y < h) {
+        const float *row = map + (size_t)y * (unsigned)w;
+        if (x >= 0 && x + 3 < w) {
+            v = ldo((const float4 *)row, (unsigned)x * 4u);
+        } else {
+            if (x >= 0 && x < w) v.x = row[x];
+            if (x + 1 >= 0 && x + 1 < w) v.y = row[x + 1];
+            if (x + 2 < w) v.z = row[x + 2];
+            if (x + 3 < w) v.w = row[x + 3];
+        }
+    }
+    tiles[(size_t)p * nx * 16u + t] = v;
 }
 
 ShadowTilesPlan shadow_tiles_plan(int w, int h) {
@@ -182,8 +193,8 @@ ShadowTilesPlan shadow_tiles_plan(int w, int h) {
 
 hipError_t launch_shadow_tiles(const float *map, int w, int h, float *tiles, hipStream_t s) {
     ShadowTilesPlan t = shadow_tiles_plan(w, h);
-    dim3 grid(ceil_div(t.nx * 64, 256), t.ny + 1);
-    k_shadow_tiles<<<grid, 256, 0, s>>>(map, w, h, t.nx, t.ny, tiles);
+    dim3 grid(ceil_div(t.nx * 16, 256), t.ny + 1);
+    k_shadow_tiles<<<grid, 256, 0, s>>>(map, w, h, t.nx, t.ny, (float4 *)tiles);
     return hipGetLastError();
 }
 
