@@ -130,19 +130,21 @@ __global__ void __launch_bounds__(64 * NX *NY) k_raycast(const RayScene s, const
         for (int k = 0; k < 3; ++k) d[j][k] = c.M[k] * v0 + c.M[4 + k] * v1 + c.M[8 + k] * v2;
         aa[j] = d[j][0] * d[j][0] + d[j][1] * d[j][1] + d[j][2] * d[j][2];
     }
-    // The cone around the wavefront's rays: axis = the mean of its corner rays (its centre ray),
-    // sin_a = the largest sine of an angle to the axis, which a corner has (the directions within an
-    // angle below 90 degrees form a convex cone).  cos_a = sin_a = 0 keeps every sphere.
-    constexpr int kC1 = kRayLx - 1, kC2 = 64 - kRayLx, kC3 = 63;
-    float3 f0 = to_float3(d[0]), f1 = to_float3(d[PPT - 1]);
-    float3 ax;
-    ax.x = from_lane(f0.x, 0) + from_lane(f0.x, kC1) + from_lane(f1.x, kC2) + from_lane(f1.x, kC3);
-    ax.y = from_lane(f0.y, 0) + from_lane(f0.y, kC1) + from_lane(f1.y, kC2) + from_lane(f1.y, kC3);
-    ax.z = from_lane(f0.z, 0) + from_lane(f0.z, kC1) + from_lane(f1.z, kC2) + from_lane(f1.z, kC3);
-    float inv = rsq(ax.x * ax.x + ax.y * ax.y + ax.z * ax.z);
-    ax.x *= inv; ax.y *= inv; ax.z *= inv;
-    float sin_a, cos_a;
-    {
+    // The cone around the wavefront's rays, made when there is a sphere to test: axis = the mean of
+    // its corner rays (its centre ray), sin_a = the largest sine of an angle to the axis, which a
+    // corner has (the directions within an angle below 90 degrees form a convex cone).  cos_a =
+    // sin_a = 0 keeps every sphere.
+    float3 ax = make_float3(0.0f, 0.0f, 0.0f);
+    float sin_a = 0.0f, cos_a = 0.0f;
+    bool have_cone = false;
+    auto make_cone = [&]() {
+        constexpr int kC1 = kRayLx - 1, kC2 = 64 - kRayLx, kC3 = 63;
+        float3 f0 = to_float3(d[0]), f1 = to_float3(d[PPT - 1]);
+        ax.x = from_lane(f0.x, 0) + from_lane(f0.x, kC1) + from_lane(f1.x, kC2) + from_lane(f1.x, kC3);
+        ax.y = from_lane(f0.y, 0) + from_lane(f0.y, kC1) + from_lane(f1.y, kC2) + from_lane(f1.y, kC3);
+        ax.z = from_lane(f0.z, 0) + from_lane(f0.z, kC1) + from_lane(f1.z, kC2) + from_lane(f1.z, kC3);
+        float inv = rsq(ax.x * ax.x + ax.y * ax.y + ax.z * ax.z);
+        ax.x *= inv; ax.y *= inv; ax.z *= inv;
         // (the lanes of the upper half hold the last row's rays, those of the lower half the first row's)
         float3 f = lane < 32 ? f0 : f1;
         float il = rsq(f.x * f.x + f.y * f.y + f.z * f.z);
@@ -153,7 +155,8 @@ __global__ void __launch_bounds__(64 * NX *NY) k_raycast(const RayScene s, const
         float cmin = fminf(fminf(from_lane(cs, 0), from_lane(cs, kC1)), fminf(from_lane(cs, kC2), from_lane(cs, kC3)));
         cos_a = sqrtf(fmaxf(1.0f - sin_a * sin_a, 0.0f));
         if (!(cmin > 0.1f)) sin_a = cos_a = 0.0f;  // (also for overflowing or undefined rays)
-    }
+        have_cone = true;
+    };
     double best[PPT], far_num[PPT];  // far_num / aa is past best
     int who[PPT];
 #pragma unroll
@@ -188,6 +191,7 @@ __global__ void __launch_bounds__(64 * NX *NY) k_raycast(const RayScene s, const
             if (n <= kList - kGroup) continue;  // another group fits behind it: the list keeps growing
             if (t == 0) list_n = 0;
         }
+        if (n > 0 && !have_cone) make_cone();
         for (int e = 0; e < n; e += 64) {
             bool keep = false;
             RayCand q{};
