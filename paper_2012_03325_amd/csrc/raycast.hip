@@ -35,9 +35,12 @@
 namespace epb {
 
 // A sphere's pixel box [x0, x1) x [y0, y1) (inside the image) and a lower bound
-// of the depth of its hits.
+// of the depth of its hits.  The box is kept as (x0, -x1) and (y0, -y1), so that
+// adding (-X1, X0) and (-Y1, Y0) to it leaves four negative halves exactly when it
+// meets the region [X0, X1) x [Y0, Y1): two packed additions, one and, one compare.
+typedef short Short2 __attribute__((ext_vector_type(2)));
 struct SphereRec {
-    unsigned x, y;  // x0 | x1 << 16, y0 | y1 << 16
+    Short2 x, y;
     float zmin;
     unsigned pad;
 };
@@ -76,8 +79,8 @@ __global__ void __launch_bounds__(256) k_sphere_records(const RayScene s, const 
     // grazing ray is off by up to sqrt(2^-53) of the distances that enter it, about 1e-8 of them
     double mag = fabs(cc[0]) + fabs(cc[1]) + fabs(cc[2]) + fabs(c.M[3]) + fabs(c.M[7]) + fabs(c.M[11]) + fabs(r);
     SphereRec q;
-    q.x = (unsigned)x0 | (unsigned)x1 << 16;
-    q.y = (unsigned)y0 | (unsigned)y1 << 16;
+    q.x = Short2{(short)x0, (short)-x1};
+    q.y = Short2{(short)y0, (short)-y1};
     q.zmin = (float)(-v[2] - fabs(r) - 4e-6 * mag);
     q.pad = 0;
     rec[k] = q;
@@ -122,6 +125,8 @@ __global__ void __launch_bounds__(64 * NX *NY) k_raycast(const RayScene s, const
     int wv = __builtin_amdgcn_readfirstlane(t >> 6);
     int x = X0 + (wv % NX) * kRayLx + lane % kRayLx, y = Y0 + (wv / NX) * kRayTy + lane / kRayLx;
     if (t == 0) list_n = 0;
+    // (the region's far edges at most 16384 + a region: 16 bits hold every sum)
+    Short2 at_x = {(short)-(X0 + kRx), (short)X0}, at_y = {(short)-(Y0 + kRy), (short)Y0};
     double d[PPT][3], aa[PPT];
     double v0 = ((double)x + 0.5 - c.cx) / c.fx;
 #pragma unroll
@@ -167,14 +172,19 @@ __global__ void __launch_bounds__(64 * NX *NY) k_raycast(const RayScene s, const
     __syncthreads();
     for (int base = 0; base < s.n; base += kGroup) {
         // the spheres of this group whose boxes meet the region, appended in any order
-        SphereRec q[kLoads];
+        Short2 bx[kLoads], by[kLoads];
 #pragma unroll
-        for (int g = 0; g < kLoads; ++g) q[g] = rec[min(base + g * kThreads + t, s.n - 1)];
+        for (int g = 0; g < kLoads; ++g) {
+            const SphereRec &q = rec[min(base + g * kThreads + t, s.n - 1)];
+            bx[g] = q.x;
+            by[g] = q.y;
+        }
 #pragma unroll
         for (int g = 0; g < kLoads; ++g) {
             int k = base + g * kThreads + t;
-            bool in = k < s.n && (int)(q[g].x & 0xffffu) < X0 + kRx && (int)(q[g].x >> 16) > X0 &&
-                      (int)(q[g].y & 0xffffu) < Y0 + kRy && (int)(q[g].y >> 16) > Y0;
+            Short2 ox = bx[g] + at_x, oy = by[g] + at_y;
+            unsigned both = __builtin_bit_cast(unsigned, ox) & __builtin_bit_cast(unsigned, oy);
+            bool in = k < s.n && (both & 0x80008000u) == 0x80008000u;
             unsigned long long m = __ballot(in);
             if (m) {
                 int at = 0;
