@@ -65,6 +65,11 @@ __device__ __forceinline__ void sto(T *base, unsigned byte_off, T v) {
         *(GS *)a = h;
     }
 }
+// Makes an offset that several blocks of a kernel use opaque in the current one: the
+// compiler forms the scalar-base address only for an offset that it widens where the
+// access is, and otherwise adds 64-bit addresses per lane.
+__device__ __forceinline__ void local_offset(unsigned &i) { asm volatile("" : "+v"(i)); }
+
 __device__ __forceinline__ float ldf(const float *base, unsigned i) { return ldo(base, i * 4u); }
 __device__ __forceinline__ float ldf(const __half *base, unsigned i) { return __half2float(ldo(base, i * 2u)); }
 __device__ __forceinline__ void stf(float *base, unsigned i, float v) { sto(base, i * 4u, v); }
@@ -182,7 +187,7 @@ __device__ __forceinline__ float4 face_bilinear(const float4 *__restrict__ lvl, 
                                                 FaceST f) {
     float x = clamp_to(fmaf(f.s, g.half, g.off), g.hi);
     float y = clamp_to(fmaf(f.t, g.half, g.off), g.hi);
-    float x0f = fminf(floorf(x), g.hi1), y0f = fminf(floorf(y), g.hi1);
+    float x0f = clamp_to(floorf(x), g.hi1), y0f = clamp_to(floorf(y), g.hi1);
     float wx = x - x0f, wy = y - y0f;
     // row of the texel in the level: face S + y0, exact in float (below 2^24)
     unsigned idx = off + __umul24((unsigned)fmaf(f.face, (float)g.S, y0f), (unsigned)g.S) + (unsigned)x0f;

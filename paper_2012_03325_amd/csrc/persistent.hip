@@ -64,7 +64,7 @@ __device__ __forceinline__ void persist_tile(const BatchHeader *h, const ViewDes
         else ssao_raw_tile<kPersistSsaoT, kPersistSsaoT, 8, T, T>(d.ssao, t);
         break;
     case kStBlur: ssao_blur_tile<kPersistSsaoT, kPersistSsaoT, T>(d.ssao, t, sm.blur.sd, sm.blur.sa); break;
-    case kStShade: shade_tile<32, 8, false, T, T, T>(d.shade, t); break;
+    case kStShade: shade_tile<32, 8, false, false, T, T, T>(d.shade, t); break;
     case kStDown: bloom_down_tile<T, TP>(d.post, t, sm.down); break;
     case kStBloomBlur: bloom_blur_item<TP>(d.post, t, sm.bloom); break;
     default: {

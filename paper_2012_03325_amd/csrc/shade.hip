@@ -34,16 +34,16 @@ namespace epb {
 // ---------------------------------------------------------------------------
 // kernels
 // ---------------------------------------------------------------------------
-// Minimum waves per SIMD: 7, the FP32 kernel's natural 65 VGPRs (69 with the
-// bloom epilogue).  At 8 (64 VGPRs) the FP16 kernel spills and runs 3 us
-// slower at 1080p; the batched kernel, with the view lookup on top, would
-// settle at 6.
+// Minimum waves per SIMD: 7.  The single-view kernels need 63 VGPRs and so run at
+// 8 (65, 7 waves, with the bloom epilogue); the batched ones, with the view lookup on
+// top, need 69 to 71 and would settle at 6, and spill at 8 (batch of 16 half views
+// 210 -> 235 us).
 constexpr int kShadeMinWaves = 7;
 
 template <int TX, int TY, bool kBloom1, typename TG, typename TA, typename TH>
 __global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(kShadeMinWaves)))
 k_shade(const ShadeDesc c, int tiles) {
-    shade_tile<TX, TY, kBloom1, TG, TA, TH>(
+    shade_tile<TX, TY, kBloom1, true, TG, TA, TH>(
         c, xcd_chunk_item((int)blockIdx.x % kNumXcd, (int)blockIdx.x / kNumXcd, tiles));
 }
 
@@ -58,7 +58,7 @@ k_shade_batch(const void *__restrict__ table) {
     for (int it = (int)blockIdx.x / kNumXcd; it < count; it += stride) {
         int g = xcd_chunk_item(x, it, total);
         int v = find_view(start, h->n_views, g);
-        shade_tile<TX, TY, kBloom1, TG, TA, TH>(views[v].shade, g - start[v]);
+        shade_tile<TX, TY, kBloom1, false, TG, TA, TH>(views[v].shade, g - start[v]);
     }
 }
 

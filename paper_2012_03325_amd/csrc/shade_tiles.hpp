@@ -17,7 +17,7 @@ __device__ __forceinline__ float2 lut_bilinear(const float2 *__restrict__ lut, c
     float fsize = (float)g.S;
     float fx = clamp_to(fmaf(u, fsize, -0.5f), g.hi);
     float fy = clamp_to(fmaf(v, fsize, -0.5f), g.hi);
-    float x0f = fminf(floorf(fx), g.hi1), y0f = fminf(floorf(fy), g.hi1);
+    float x0f = clamp_to(floorf(fx), g.hi1), y0f = clamp_to(floorf(fy), g.hi1);
     float wx = fx - x0f, wy = fy - y0f;
     unsigned o0 = (__umul24((unsigned)y0f, (unsigned)g.S) + (unsigned)x0f) * 8u;
     unsigned o1 = o0 + (unsigned)g.S * 8u;
@@ -60,8 +60,9 @@ __device__ __forceinline__ float pcf(const DevLight &L, float dvx, float dvy, fl
         int i0 = floor_to_int(u), j0 = floor_to_int(v);
         bool inside = dl > 0.0f && (unsigned)i0 < (unsigned)L.w && (unsigned)j0 < (unsigned)L.h;
         unsigned x = (unsigned)i0, y = (unsigned)j0;
-        unsigned tq = __umulhi(x, 0x2AAAAAABu), tp = __umulhi(y, 0x2AAAAAABu);  // x / 6, y / 6 (exact below 2^31)
-        unsigned q0 = inside ? __umul24(tp, L.tile_pitch) + __umul24(tq, 232u) + y * 32u + x * 4u : L.sentinel;
+        // x / 6, y / 6 (exact below 2^15; the high half of a 32-bit product is a quarter-rate instruction)
+        unsigned tq = __umul24(x, 43691u) >> 18, tp = __umul24(y, 43691u) >> 18;
+        unsigned q0 = inside ? __umul24(tp, L.tile_pitch) + (__umul24(tq, 232u) + x * 4u) + y * 32u : L.sentinel;
         const char *base = reinterpret_cast<const char *>(L.map);  // wave-uniform: the row offsets are scalar adds
         Row3 a = ldo(map, q0), b = ldo(reinterpret_cast<const Row3 *>(base + 32), q0),
              e = ldo(reinterpret_cast<const Row3 *>(base + 64), q0);
@@ -94,8 +95,23 @@ __device__ __forceinline__ float pcf(const DevLight &L, float dvx, float dvy, fl
     return inside ? (float)lit * (1.0f / 9.0f) : 1.0f;
 }
 
+// Channel k of a planar image at pixel p.  With kBases the planes are scalar bases
+// under one vector offset, which the single-view kernels take (63 registers and so
+// 8 waves per SIMD where offsets per plane need 65: 3840x2160 half 168 -> 161 us);
+// in the batched kernels, whose bases come from the table, they cost registers (the
+// one with the bloom epilogue spills: batch of 16 half views 385 -> 397 us).
+template <bool kBases, typename T>
+__device__ __forceinline__ float ld_plane(const T *b, unsigned plane, unsigned k, unsigned p) {
+    return kBases ? ldf(b + k * (size_t)plane, p) : ldf(b, k * plane + p);
+}
+template <bool kBases, typename T>
+__device__ __forceinline__ void st_plane(T *b, unsigned plane, unsigned k, unsigned p, float v) {
+    if (kBases) stf(b + k * (size_t)plane, p, v);
+    else stf(b, k * plane + p, v);
+}
+
 // One pixel's radiance: shading of the surface, or the environment behind it.
-template <typename TG, typename TA, typename TH>
+template <bool kBases, typename TG, typename TA, typename TH>
 __device__ __forceinline__ void shade_pixel(const ShadeDesc &c, int x, int y, float (&out)[3]) {
     unsigned p = __umul24((unsigned)y, (unsigned)c.W) + (unsigned)x;
     unsigned plane = (unsigned)c.W * (unsigned)c.H;
@@ -107,13 +123,14 @@ __device__ __forceinline__ void shade_pixel(const ShadeDesc &c, int x, int y, fl
         float4 e = cube_bilinear(c.env, c.env_dims, dw);
         out[0] = e.x; out[1] = e.y; out[2] = e.z;
     } else {
+        if (kBases) local_offset(p);
         const TG *nrm = (const TG *)c.normal, *alb = (const TG *)c.albedo;
         v3 Pv = mk3(dvx * d, dvy * d, -d);
         v3 Pr = mul_Rt(c.R, Pv);  // world position relative to the camera
         v3 Pw = Pr + mk3(c.cam_pos[0], c.cam_pos[1], c.cam_pos[2]);
         v3 V = normalize(mk3(-Pr.x, -Pr.y, -Pr.z));
-        v3 n = normalize(mk3(ldf(nrm, p), ldf(nrm, plane + p), ldf(nrm, 2 * plane + p)));
-        float a[3] = {ldf(alb, p), ldf(alb, plane + p), ldf(alb, 2 * plane + p)};
+        v3 n = normalize(mk3(ldf(nrm, p), ld_plane<kBases>(nrm, plane, 1, p), ld_plane<kBases>(nrm, plane, 2, p)));
+        float a[3] = {ldf(alb, p), ld_plane<kBases>(alb, plane, 1, p), ld_plane<kBases>(alb, plane, 2, p)};
         float r = ldf((const TG *)c.rough, p);
         float mt = ldf((const TG *)c.metal, p);
         if (c.weight) {  // surfel G-buffer: accumulated attributes over their weight
@@ -210,10 +227,11 @@ __device__ __forceinline__ void shade_pixel(const ShadeDesc &c, int x, int y, fl
             out[ch] = fmaf(ao, amb, Lo[ch]);
         }
     }
+    if (kBases) local_offset(p);
     TH *hdr = (TH *)c.hdr;
     stf(hdr, p, out[0]);
-    stf(hdr, plane + p, out[1]);
-    stf(hdr, 2 * plane + p, out[2]);
+    st_plane<kBases>(hdr, plane, 1, p, out[1]);
+    st_plane<kBases>(hdr, plane, 2, p, out[2]);
 }
 
 // Level 1 of the bloom pyramid from the shaded pixels of this wave: the texel
@@ -245,7 +263,7 @@ __device__ __forceinline__ void bloom1_epilogue(const ShadeDesc &c, int x, int y
     }
 }
 
-template <int TX, int TY, bool kBloom1, typename TG, typename TA, typename TH>
+template <int TX, int TY, bool kBloom1, bool kBases, typename TG, typename TA, typename TH>
 __device__ __forceinline__ void shade_tile(const ShadeDesc &c, int tile) {
     int tiles_x = (c.W + TX - 1) / TX;
     int ty = tile / tiles_x;
@@ -255,7 +273,7 @@ __device__ __forceinline__ void shade_tile(const ShadeDesc &c, int tile) {
     float out[3] = {0.0f, 0.0f, 0.0f};
     // (with kBloom1 every lane reaches the epilogue; otherwise out-of-image lanes leave here)
     if (!kBloom1 && !in) return;
-    if (in) shade_pixel<TG, TA, TH>(c, x, y, out);
+    if (in) shade_pixel<kBases, TG, TA, TH>(c, x, y, out);
     if constexpr (kBloom1) {
         if (c.bloom1) bloom1_epilogue<TX, TH>(c, x, y, in, out);  // (uniform: null for a view without bloom)
     }
