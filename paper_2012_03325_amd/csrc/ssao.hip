@@ -29,6 +29,7 @@
 //    sample is discarded by its range test).
 //  * blur: 4x4 bilateral mean; the 19x11 depth/AO footprint of a 16x8 tile is
 //    staged through LDS.
+//  * raw and blur in one kernel for small images (see ssao_fused_tile).
 //  * every stage has a single-view kernel (one block per tile, XCD-aware
 //    order) and a batched kernel that walks the tiles of many views.
 #include <mutex>
@@ -56,6 +57,13 @@ __global__ void __launch_bounds__(kBlurTx *kBlurTy) k_ssao_blur(const SsaoDesc c
     __shared__ float sd[blur_lds_rows<kBlurTx, kBlurTy>()][kBlurTx + 3];
     __shared__ float sa[blur_lds_rows<kBlurTx, kBlurTy>()][kBlurTx + 3];
     ssao_blur_tile<kBlurTx, kBlurTy, TA>(c, xcd_tile(blockIdx.x, tiles), sd, sa);
+}
+
+template <int TX, int TY, int KB, typename TG, typename TA>
+__global__ void __launch_bounds__(ssao_fused_threads(TX, TY)) k_ssao_raw_blur(const SsaoDesc c, int tiles) {
+    __shared__ float sd[TY + 3][TX + 3];
+    __shared__ float sa[TY + 3][TX + 3];
+    ssao_raw_blur_tile<TX, TY, KB, TG, TA>(c, xcd_tile(blockIdx.x, tiles), sd, sa);
 }
 
 // ---------------------------------------------------------------------------
@@ -201,7 +209,49 @@ static void go_raw(const SsaoDesc &c, hipStream_t s) {
     hipLaunchKernelGGL((k_ssao_raw<TX, TY, KB, TG, TA>), dim3(tiles), dim3(TX * TY), 0, s, c, tiles);
 }
 
+// Tile of the kernel that makes raw AO and blur in one, 0 for the two kernels.  Its wavefronts
+// also form the footprints' margins, so that it has more of them: R per SIMD where the raw
+// kernel has w (1024 SIMDs).  A wavefront takes about 0.04 us per sample, a second launch and
+// reading the raw values back about 2.7 us, hence n (R - w) <= 64.  SSAO with the blur, two
+// kernels against one: 640x480, 16 / 64 / 128 samples 8.6 / 13.4 / 20.7 and 5.4 / 11.4 / 19.2 us;
+// 800x600, 64 samples 14.1 / 13.7, 128 samples 21.5 / 23.5 (not taken); 1003x667, 64 samples 18.3 /
+// 16.8; 1280x720, 16 samples 9.8 / 8.8, 32 samples equal, 64 samples 19.4 / 22.0 (not taken).  13 x
+// 13 tiles have a footprint of exactly four wavefronts: better than 16 x 8, 16 x 16 or 29 x 13 up to
+// 1280x720.  8 x 8 while every tile has a CU of its own: 256x256, 64 samples 10.7 us with two
+// kernels, 9.6 with 13 x 13 tiles, 8.7; 320x240 (300 tiles) 11.6, 9.6, 10.5.
+constexpr int kSsaoFusedTile = 13, kSsaoFusedSmallTile = 8;
+
+static int ssao_fused_tile(const SsaoDesc &c) {
+    if (!c.blur || c.hcompact) return 0;
+    auto tiles = [&](int tx, int ty) { return (long)ceil_div(c.Wh, tx) * ceil_div(c.Hh, ty); };
+    if (tiles(kSsaoFusedSmallTile, kSsaoFusedSmallTile) <= 256) return kSsaoFusedSmallTile;
+    long fused = (tiles(kSsaoFusedTile, kSsaoFusedTile) + 255) / 256, raw = (tiles(16, 8) + 511) / 512;
+    return (long)c.n * (fused - raw) <= 64 ? kSsaoFusedTile : 0;
+}
+
+template <int T, typename TG, typename TA>
+static void go_raw_blur(const SsaoDesc &c, hipStream_t s) {
+    int tiles = ceil_div(c.Wh, T) * ceil_div(c.Hh, T);
+    hipLaunchKernelGGL((k_ssao_raw_blur<T, T, 8, TG, TA>), dim3(tiles), dim3(ssao_fused_threads(T, T)), 0, s, c, tiles);
+}
+
+template <typename TG, typename TA>
+static void pick_raw_blur(const SsaoDesc &c, int tile, hipStream_t s) {
+    if (tile == kSsaoFusedSmallTile) go_raw_blur<kSsaoFusedSmallTile, TG, TA>(c, s);
+    else go_raw_blur<kSsaoFusedTile, TG, TA>(c, s);
+}
+
 hipError_t launch_ssao(const SsaoDesc &c, epb_dtype gdtype, epb_dtype ao_dtype, hipStream_t s) {
+    if (int tile = ssao_fused_tile(c)) {
+        if (gdtype == EPB_F32) {
+            if (ao_dtype == EPB_F32) pick_raw_blur<float, float>(c, tile, s);
+            else pick_raw_blur<float, __half>(c, tile, s);
+        } else {
+            if (ao_dtype == EPB_F32) pick_raw_blur<__half, float>(c, tile, s);
+            else pick_raw_blur<__half, __half>(c, tile, s);
+        }
+        return hipGetLastError();
+    }
     int prep = ssao_items(c, kStPrep, 0);
     if (c.hcompact) hipLaunchKernelGGL(k_ssao_prep, dim3(prep), dim3(kSsaoPrepW), 0, s, c, prep);
     // the raw pass writes float32 into scratch when a blur follows

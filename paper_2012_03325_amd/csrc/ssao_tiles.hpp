@@ -194,6 +194,36 @@ constexpr int blur_lds_rows() {
     return ((TY + 3) * (TX + 3) + TX * TY - 1) / (TX * TY) * (TX * TY) / (TX + 3) + 1;
 }
 
+// 4x4 bilateral mean of half-resolution texel (i, j): rows sd[0 .. 3], sa[0 .. 3] and
+// columns ti .. ti + 3 of the staged depths and raw values are its neighbourhood, itself
+// at [2][ti + 2].
+template <int TX, typename TA>
+__device__ __forceinline__ void ssao_blur_texel(const SsaoDesc &c, int i, int j, float (*sd)[TX + 3],
+                                                float (*sa)[TX + 3], int ti) {
+    float dp = sd[2][ti + 2];
+    float v = 1.0f;
+    if (!__builtin_isinf(dp)) {
+        float inv = rcp(c.tau * dp);  // weight 1 - |d_q - d_p| / (tau d_p)
+        float s = 0.0f, sw = 0.0f;
+#pragma unroll
+        for (int dy = 0; dy < 4; ++dy)
+#pragma unroll
+            for (int dx = 0; dx < 4; ++dx) {
+                // a background or out-of-range neighbour (+inf) gets max(0, -inf) = 0
+                float dq = sd[dy][ti + dx];
+                float w = fmaxf(0.0f, 1.0f - fabsf(dq - dp) * inv);
+                s = fmaf(w, sa[dy][ti + dx], s);
+                sw += w;
+            }
+        // s / sw (sw >= 1: the centre's own weight) from the reciprocal and one
+        // correction with the exact residual s - sw q: exactly 1 where s == sw, and
+        // kept in [0, 1] (a weighted mean of values in [0, 1]) by the free clamp
+        float r = rcp(sw), q = s * r;
+        v = clamp01(fmaf(fmaf(-sw, q, s), r, q));
+    }
+    stf((TA *)c.out, __umul24((unsigned)j, (unsigned)c.Wh) + (unsigned)i, v);
+}
+
 // 4x4 bilateral mean of one TX x TY tile of half-resolution texels (TX * TY
 // threads); the same arithmetic per texel for every tile shape.
 template <int TX, int TY, typename TA>
@@ -226,31 +256,36 @@ __device__ __forceinline__ void ssao_blur_tile(const SsaoDesc &c, int tile, floa
     __syncthreads();
     int ti = threadIdx.x % TX, tj = threadIdx.x / TX;
     int i = i0 + ti, j = j0 + tj;
-    if (i < c.Wh && j < c.Hh) {
-        float dp = sd[tj + 2][ti + 2];
-        float v = 1.0f;
-        if (!__builtin_isinf(dp)) {
-            float inv = rcp(c.tau * dp);  // weight 1 - |d_q - d_p| / (tau d_p)
-            float s = 0.0f, sw = 0.0f;
-#pragma unroll
-            for (int dy = 0; dy < 4; ++dy)
-#pragma unroll
-                for (int dx = 0; dx < 4; ++dx) {
-                    // a background or out-of-range neighbour (+inf) gets max(0, -inf) = 0
-                    float dq = sd[tj + dy][ti + dx];
-                    float w = fmaxf(0.0f, 1.0f - fabsf(dq - dp) * inv);
-                    s = fmaf(w, sa[tj + dy][ti + dx], s);
-                    sw += w;
-                }
-            // s / sw (sw >= 1: the centre's own weight) from the reciprocal and one
-            // correction with the exact residual s - sw q: exactly 1 where s == sw, and
-            // kept in [0, 1] (a weighted mean of values in [0, 1]) by the free clamp
-            float r = rcp(sw), q = s * r;
-            v = clamp01(fmaf(fmaf(-sw, q, s), r, q));
-        }
-        stf((TA *)c.out, __umul24((unsigned)j, (unsigned)c.Wh) + (unsigned)i, v);
-    }
+    if (i < c.Wh && j < c.Hh) ssao_blur_texel<TX, TA>(c, i, j, sd + tj, sa + tj, ti);
     __syncthreads();  // the tile's LDS may be refilled by the next item
+}
+
+// Raw AO and blur of one TX x TY tile: the raw values of its (TX + 3) x (TY + 3) footprint
+// go to LDS only (neighbouring tiles form the shared ones again, by the same arithmetic).
+// One thread per footprint texel.
+constexpr int ssao_fused_threads(int tx, int ty) { return ((tx + 3) * (ty + 3) + 63) / 64 * 64; }
+template <int TX, int TY, int KB, typename TG, typename TA>
+__device__ __forceinline__ void ssao_raw_blur_tile(const SsaoDesc &c, int tile, float (*sd)[TX + 3], float (*sa)[TX + 3]) {
+    constexpr int LW = TX + 3, LH = TY + 3;  // offsets -2 .. +1
+    int tiles_x = (c.Wh + TX - 1) / TX;
+    int ty = tile / tiles_x;
+    int i0 = (tile - ty * tiles_x) * TX, j0 = ty * TY;
+    int li = (int)threadIdx.x % LW, lj = (int)threadIdx.x / LW;
+    if (lj < LH) {
+        int i = i0 + li - 2, j = j0 + lj - 2;
+        float d = __builtin_inff(), a = 0.0f;  // out of range: weight 0
+        if (i >= 0 && i < c.Wh && j >= 0 && j < c.Hh) {
+            unsigned p = __umul24((unsigned)(2 * j), (unsigned)c.W) + (unsigned)(2 * i);
+            d = ldf(c.depth, p);
+            a = __builtin_isinf(d) ? 1.0f : ssao_texel<KB, false, TG>(c, i, j, p, d, LdsWindow{});
+        }
+        sd[lj][li] = d;
+        sa[lj][li] = a;
+    }
+    __syncthreads();
+    int ti = (int)threadIdx.x % TX, tj = (int)threadIdx.x / TX;
+    if (tj < TY && i0 + ti < c.Wh && j0 + tj < c.Hh)
+        ssao_blur_texel<TX, TA>(c, i0 + ti, j0 + tj, sd + tj, sa + tj, ti);
 }
 
 }  // namespace epb
