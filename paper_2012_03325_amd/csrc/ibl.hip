@@ -439,6 +439,31 @@ __device__ __forceinline__ void prefilter_block(int block, int blocks, const Rgb
     }
 }
 
+// face_bilinear split into its loads and its interpolation, so that several lookups'
+// loads can be in flight: the same coordinates, taps and interpolation.
+struct LevelTaps {
+    float4 a, b, c, d;
+    float wx, wy;
+};
+__device__ __forceinline__ LevelTaps level_taps(const float4 *__restrict__ lvl, const FaceDims &g, FaceST f) {
+    LevelTaps q;
+    float x = clamp_to(fmaf(f.s, g.half, g.off), g.hi);
+    float y = clamp_to(fmaf(f.t, g.half, g.off), g.hi);
+    float x0f = clamp_to(floorf(x), g.hi1), y0f = clamp_to(floorf(y), g.hi1);
+    q.wx = x - x0f;
+    q.wy = y - y0f;
+    unsigned idx = __umul24((unsigned)fmaf(f.face, (float)g.S, y0f), (unsigned)g.S) + (unsigned)x0f;
+    unsigned o0 = idx * 16u, o1 = o0 + (unsigned)g.S * 16u;
+    q.a = ldo(lvl, o0);
+    q.b = ldo(lvl + 1, o0);
+    q.c = ldo(lvl, o1);
+    q.d = ldo(lvl + 1, o1);
+    return q;
+}
+__device__ __forceinline__ float4 level_value(const LevelTaps &q) {
+    return lerp4(lerp4(q.a, q.b, q.wx), lerp4(q.c, q.d, q.wx), q.wy);
+}
+
 // Partial sums of a prefiltered level (roughness > 0) with filtered importance
 // sampling.  Wavefront w of the grid takes tile w / chunks (8x8 texels of one
 // face) and chunk w % chunks of the samples; its lanes are the tile's texels (a
@@ -468,25 +493,40 @@ __device__ __forceinline__ void prefilter_fis_block(int block, const float4 *__r
     Kahan r{0, 0}, g{0, 0}, b{0, 0}, wt{0, 0};
     // (samples <= 2^20 and chunks <= 16: the products fit in 32 bits)
     int k0 = chunk * samples / chunks, k1 = (chunk + 1) * samples / chunks;
-    for (int k = k0; k < k1; ++k) {
-        float4 tk = table[k];
-        v3 h = ggx_to_world(tk, n, T, B);
-        float vh = dot(n, h);
-        v3 l = h * (2.0f * vh) - n;
-        float nl = dot(n, l);
-        if (nl > 0.0f) {
-            float lod = tk.w;  // the sample's, so wave-uniform
+    // two samples at a time, so that their taps are in flight together (the adds keep the
+    // samples' order): the whole precompute of a 6x512^2 cube with 1024 samples takes 254 us,
+    // with one at a time 275, with four (148 registers) 268
+    constexpr int kFisRun = 2;
+    const ConstFloat *tab = as_constant((const float *)table);
+    for (int k = k0; k < k1; k += kFisRun) {
+        LevelTaps t0[kFisRun], t1[kFisRun];
+        float nl[kFisRun], fl[kFisRun];
+#pragma unroll
+        for (int u = 0; u < kFisRun; ++u) {
+            const ConstFloat *e = tab + 4 * min(k + u, k1 - 1);
+            float lod = e[3];  // the sample's, so wave-uniform
+            v3 h = ggx_to_world(make_float4(e[0], e[1], e[2], 0.0f), n, T, B);
+            float vh = dot(n, h);
+            v3 l = h * (2.0f * vh) - n;
+            nl[u] = k + u < k1 ? dot(n, l) : 0.0f;
             int l0 = __builtin_amdgcn_readfirstlane((int)lod);
             int l1 = min(l0 + 1, last);
-            float fl = lod - (float)l0;
-            FaceST fs = cube_face(l);
-            float4 L0 = face_bilinear(l0 ? chain + chain_offset_pow2(S, l0) : env, 0u, face_dims(S >> l0), fs);
-            float4 L1 = face_bilinear(l1 ? chain + chain_offset_pow2(S, l1) : env, 0u, face_dims(S >> l1), fs);
-            float4 L = lerp4(L0, L1, fl);
-            kahan_add(r, L.x * nl);
-            kahan_add(g, L.y * nl);
-            kahan_add(b, L.z * nl);
-            kahan_add(wt, nl);
+            fl[u] = lod - (float)l0;
+            if (nl[u] > 0.0f) {
+                FaceST fs = cube_face(l);
+                t0[u] = level_taps(l0 ? chain + chain_offset_pow2(S, l0) : env, face_dims(S >> l0), fs);
+                t1[u] = level_taps(l1 ? chain + chain_offset_pow2(S, l1) : env, face_dims(S >> l1), fs);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kFisRun; ++u) {
+            if (nl[u] > 0.0f) {
+                float4 L = lerp4(level_value(t0[u]), level_value(t1[u]), fl[u]);
+                kahan_add(r, L.x * nl[u]);
+                kahan_add(g, L.y * nl[u]);
+                kahan_add(b, L.z * nl[u]);
+                kahan_add(wt, nl[u]);
+            }
         }
     }
     if (i < sm && j < sm) {
