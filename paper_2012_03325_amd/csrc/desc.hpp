@@ -88,7 +88,7 @@ struct ShadeDesc {
     int n_lights;
     DevLight lights[EPB_MAX_LIGHTS];
     void *bloom1;           // bloom level 1, written by the fused form; null otherwise
-    int bloom1_half;        // its texels are four halves (else float4)
+    int bloom1_half;        // its texels are four halves (else three floats)
     float bloom_threshold;
 };
 
@@ -96,7 +96,7 @@ struct PostDesc {
     int W, H, nl;  // nl = number of pyramid levels >= 1
     int texel_half;  // pyramid texels are four halves (else float4)
     int lw[EPB_MAX_BLOOM_LEVELS], lh[EPB_MAX_BLOOM_LEVELS];
-    void *raw[EPB_MAX_BLOOM_LEVELS];   // unblurred level texels (pyramid storage type)
+    void *raw[EPB_MAX_BLOOM_LEVELS];   // unblurred level texels (RawTexel of the pyramid's)
     void *blur[EPB_MAX_BLOOM_LEVELS];  // blurred level texels
     int blk_start[EPB_MAX_BLOOM_LEVELS + 1];  // first blur work item of each level
     float threshold, strength, exposure, inv_gamma;

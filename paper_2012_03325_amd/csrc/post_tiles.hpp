@@ -11,6 +11,10 @@ __device__ __forceinline__ float4 add4(float4 a, float4 b) {
 }
 __device__ __forceinline__ float4 scale4(float4 a, float s) { return make_float4(a.x * s, a.y * s, a.z * s, 0.0f); }
 
+__device__ __forceinline__ unsigned level_texel(const PostDesc &c, int L, int X, int Y) {
+    return __umul24((unsigned)Y, (unsigned)c.lw[L]) + (unsigned)X;
+}
+
 // ---------------------------------------------------------------------------
 // bloom_down: one 16x16 level-1 tile (32x32 pixels) -> levels 1..5 of that tile
 // ---------------------------------------------------------------------------
@@ -25,6 +29,7 @@ struct DownLds {
 // children in `src`; kept in `dst` for the next level when that is non-null.
 template <int L, int N, typename TP, typename SRC, typename DST>
 __device__ __forceinline__ void down_level(const PostDesc &c, int bx, int by, SRC src, DST dst) {
+    typedef typename RawTexel<TP>::type TR;
     int t = threadIdx.x;
     if (t >= N * N) return;
     int lx = t % N, ly = t / N;
@@ -39,7 +44,7 @@ __device__ __forceinline__ void down_level(const PostDesc &c, int bx, int by, SR
         if (y1) v = add4(v, src[2 * ly + 1][2 * lx]);
         if (x1 && y1) v = add4(v, src[2 * ly + 1][2 * lx + 1]);
         v = scale4(v, (x1 ? 0.5f : 1.0f) * (y1 ? 0.5f : 1.0f));
-        sto((TP *)c.raw[L], (unsigned)(Y * c.lw[L] + X) * (unsigned)sizeof(TP), pack<TP>(v));
+        sto((TR *)c.raw[L], level_texel(c, L, X, Y) * (unsigned)sizeof(TR), pack<TR>(v));
     }
     if (dst) dst[ly][lx] = v;
 }
@@ -83,6 +88,7 @@ __device__ __forceinline__ void ld_pair(const __half *b, unsigned p, float &u, f
 
 template <typename TH, typename TP>
 __device__ __forceinline__ void bloom_down_tile(const PostDesc &c, int tile, DownLds &sm) {
+    typedef typename RawTexel<TP>::type TR;
     int tiles_x = (c.lw[1] + kDownTile - 1) / kDownTile;
     int by = tile / tiles_x, bx = tile - by * tiles_x;
     int t = threadIdx.x;
@@ -129,8 +135,8 @@ __device__ __forceinline__ void bloom_down_tile(const PostDesc &c, int tile, Dow
         float inv_n = (in[1] ? 0.5f : 1.0f) * (in[2] ? 0.5f : 1.0f);
         v = make_float4(((cr[0] + cr[1]) + (cr[2] + cr[3])) * inv_n, ((cg[0] + cg[1]) + (cg[2] + cg[3])) * inv_n,
                         ((cb[0] + cb[1]) + (cb[2] + cb[3])) * inv_n, 0.0f);
-        TP st = pack<TP>(v);
-        sto((TP *)c.raw[1], (unsigned)(Y * c.lw[1] + X) * (unsigned)sizeof(TP), st);
+        TR st = pack<TR>(v);
+        sto((TR *)c.raw[1], level_texel(c, 1, X, Y) * (unsigned)sizeof(TR), st);
         v = unpack(st);  // the next levels average what level 1 holds
     }
     sm.s1[ly][lx] = v;
@@ -146,8 +152,8 @@ __device__ __forceinline__ void bloom_down_from1_tile(const PostDesc &c, int til
     int lx = t % kDownTile, ly = t / kDownTile;
     int X = bx * kDownTile + lx, Y = by * kDownTile + ly;
     float4 v = make_float4(0, 0, 0, 0);
-    if (X < c.lw[1] && Y < c.lh[1])
-        v = unpack(ldo((const TP *)c.raw[1], (unsigned)(Y * c.lw[1] + X) * (unsigned)sizeof(TP)));
+    typedef typename RawTexel<TP>::type TR;
+    if (X < c.lw[1] && Y < c.lh[1]) v = unpack(ldo((const TR *)c.raw[1], level_texel(c, 1, X, Y) * (unsigned)sizeof(TR)));
     sm.s1[ly][lx] = v;
     down_levels_2_to_5<TP>(c, bx, by, sm);
 }
@@ -155,18 +161,15 @@ __device__ __forceinline__ void bloom_down_from1_tile(const PostDesc &c, int til
 // ---------------------------------------------------------------------------
 // bloom_blur: one 32x16 tile of one level
 // ---------------------------------------------------------------------------
-struct Rgb {
-    float x, y, z;
-};
 constexpr int kBbW = kBloomTx + 4, kBbH = kBloomTy + 4;  // footprint with the 2-texel halo
 constexpr int kBbLdsRows = ((kBbH * kBbW + 255) / 256 * 256 + kBbW - 1) / kBbW;  // padding for whole rounds
 struct BlurLds {
-    Rgb in[kBbLdsRows][kBbW];
-    Rgb h[kBbH][kBloomTx];
+    PackedRgb in[kBbLdsRows][kBbW];
+    PackedRgb h[kBbH][kBloomTx];
 };
 
-__device__ __forceinline__ Rgb binomial5(Rgb a, Rgb b, Rgb m, Rgb d, Rgb e) {
-    return Rgb{(a.x + e.x + 4.0f * (b.x + d.x) + 6.0f * m.x) * 0.0625f,
+__device__ __forceinline__ PackedRgb binomial5(PackedRgb a, PackedRgb b, PackedRgb m, PackedRgb d, PackedRgb e) {
+    return PackedRgb{(a.x + e.x + 4.0f * (b.x + d.x) + 6.0f * m.x) * 0.0625f,
                (a.y + e.y + 4.0f * (b.y + d.y) + 6.0f * m.y) * 0.0625f,
                (a.z + e.z + 4.0f * (b.z + d.z) + 6.0f * m.z) * 0.0625f};
 }
@@ -180,23 +183,24 @@ __device__ __forceinline__ void bloom_blur_item(const PostDesc &c, int item, Blu
     int tx = (w + kBloomTx - 1) / kBloomTx;
     int ty = local / tx;
     int X0 = (local - ty * tx) * kBloomTx, Y0 = ty * kBloomTy;
-    const TP *src = (const TP *)c.raw[L];
+    typedef typename RawTexel<TP>::type TR;
+    const TR *src = (const TR *)c.raw[L];
     int t = threadIdx.x;
     // every load of the footprint in flight together: all issued before the first LDS store
     constexpr int kN = kBbH * kBbW, kIt = (kN + 255) / 256;
-    TP v[kIt];
+    TR v[kIt];
 #pragma unroll
     for (int i = 0; i < kIt; ++i) {
         int q = min(t + 256 * i, kN - 1);  // clamped: every lane issues every load
         int r = q / kBbW, cc = q - r * kBbW;
         int gy = min(max(Y0 + r - 2, 0), h - 1);
         int gx = min(max(X0 + cc - 2, 0), w - 1);
-        v[i] = ldo(src, (__umul24((unsigned)gy, (unsigned)w) + (unsigned)gx) * (unsigned)sizeof(TP));
+        v[i] = ldo(src, (__umul24((unsigned)gy, (unsigned)w) + (unsigned)gx) * (unsigned)sizeof(TR));
     }
 #pragma unroll
     for (int i = 0; i < kIt; ++i) {  // unconditional: entries past the footprint land in the padding rows
         float4 f = unpack(v[i]);
-        (&sm.in[0][0])[t + 256 * i] = Rgb{f.x, f.y, f.z};
+        (&sm.in[0][0])[t + 256 * i] = PackedRgb{f.x, f.y, f.z};
     }
     __syncthreads();
     for (int q = t; q < kBbH * kBloomTx; q += 256) {
@@ -208,8 +212,8 @@ __device__ __forceinline__ void bloom_blur_item(const PostDesc &c, int item, Blu
         int oy = q / kBloomTx, ox = q % kBloomTx;
         int X = X0 + ox, Y = Y0 + oy;
         if (X < w && Y < h) {
-            Rgb v = binomial5(sm.h[oy][ox], sm.h[oy + 1][ox], sm.h[oy + 2][ox], sm.h[oy + 3][ox], sm.h[oy + 4][ox]);
-            sto((TP *)c.blur[L], (unsigned)(Y * w + X) * (unsigned)sizeof(TP), pack<TP>(make_float4(v.x, v.y, v.z, 0.0f)));
+            PackedRgb v = binomial5(sm.h[oy][ox], sm.h[oy + 1][ox], sm.h[oy + 2][ox], sm.h[oy + 3][ox], sm.h[oy + 4][ox]);
+            sto((TP *)c.blur[L], level_texel(c, L, X, Y) * (unsigned)sizeof(TP), pack<TP>(make_float4(v.x, v.y, v.z, 0.0f)));
         }
     }
     __syncthreads();  // the next item of a batched launch refills the LDS
@@ -416,7 +420,8 @@ __device__ __forceinline__ void composite_tile(const PostDesc &c, int tile, int 
     // {2, 3} (107; the scheduler would otherwise interleave loads and uses).  Four waves
     // per SIMD are about what 1920x1080 has to give.  One trip per level: bloom and tone
     // mapping of 1920x1080 float 26.8 us against 26.3, of 3840x2160 half 61.8 against
-    // 58.9; float texels in one trip need 140 registers (26.7).
+    // 58.9; float texels in one trip need 140 registers (26.7);
+    // float figures with unblurred levels of four floats.
     float acc[kPostTy][3];
     LevelTexels<4, TP> t4;
     LevelTexels<5, TP> t5;

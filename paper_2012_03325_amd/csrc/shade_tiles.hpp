@@ -259,7 +259,7 @@ __device__ __forceinline__ void bloom1_epilogue(const ShadeDesc &c, int x, int y
         unsigned t = __umul24((unsigned)(y >> 1), (unsigned)c.Wh) + (unsigned)(x >> 1);
         float4 v = make_float4(cr * inv_n, cg * inv_n, cb * inv_n, 0.0f);
         if (c.bloom1_half) sto((Half4 *)c.bloom1, t * 8u, pack_half4(v));
-        else sto((float4 *)c.bloom1, t * 16u, v);
+        else sto((PackedRgb *)c.bloom1, t * (unsigned)sizeof(PackedRgb), pack<PackedRgb>(v));
     }
 }
 
