@@ -70,7 +70,7 @@ __device__ __forceinline__ void persist_tile(const BatchHeader *h, const ViewDes
     default: {
         int tiles = ((d.post.W + kPostTx - 1) / kPostTx) * ((d.post.H + kPostTy - 1) / kPostTy);
         int tile = t * kPersistCompositeTiles + (int)(threadIdx.x / kPostTx);
-        if (tile < tiles) composite_tile<false, T, TP>(d.post, tile, (int)(threadIdx.x % kPostTx));
+        if (tile < tiles) composite_tile<false, WholeStrip, T, TP>(d.post, tile, (int)(threadIdx.x % kPostTx));
     }
     }
 }

@@ -14,7 +14,8 @@
 //    of 8 pixels; every blurred level is interpolated at the column (rows
 //    first, then between two rows per pixel) in registers; each thread adds
 //    the upsampled levels to its pixels, applies exposure, the ACES fit,
-//    gamma and 8-bit rounding, and writes one 32-bit RGBA word per pixel.
+//    gamma and 8-bit rounding, and writes one 32-bit RGBA word per pixel
+//    (small images: half a strip per wavefront, see kCompositeHalfStrips).
 //  * pyramid texels are float4, or four halves in the FP16 form.
 //  * every stage has a single-view kernel and a batched kernel that walks the
 //    work items of many views.
@@ -47,7 +48,16 @@ __global__ void __launch_bounds__(256) k_bloom_blur(const PostDesc c) {
 
 template <typename TH, typename TP>
 __global__ void __launch_bounds__(kPostTx) __attribute__((amdgpu_waves_per_eu(4))) k_composite(const PostDesc c, int tiles) {
-    composite_tile<sizeof(TP) == 8, TH, TP>(c, xcd_tile(blockIdx.x, tiles), (int)threadIdx.x);
+    composite_tile<sizeof(TP) == 8, WholeStrip, TH, TP>(c, xcd_tile(blockIdx.x, tiles), (int)threadIdx.x);
+}
+
+// Half a strip per wavefront (see kCompositeHalfStrips).
+template <typename TH, typename TP>
+__global__ void __launch_bounds__(kPostTx) k_composite_halves(const PostDesc c, int halves) {
+    constexpr int kHalf = kPostTy / 2;
+    int b = xcd_tile(blockIdx.x, halves), lane = (int)threadIdx.x;
+    if (b & 1) composite_tile<true, StripRows<kHalf, kHalf>, TH, TP>(c, b >> 1, lane);
+    else composite_tile<true, StripRows<0, kHalf>, TH, TP>(c, b >> 1, lane);
 }
 
 template <typename TH, typename TP>
@@ -101,7 +111,7 @@ __global__ void __launch_bounds__(kPostTx) __attribute__((amdgpu_waves_per_eu(4)
     for (int it = w.lb; it < w.count; it += w.stride) {
         int g = w.first + it;
         int v = find_view(start, h->n_views, g);
-        composite_tile<sizeof(TP) == 8, TH, TP>(views[v].post, g - start[v], (int)threadIdx.x);
+        composite_tile<sizeof(TP) == 8, WholeStrip, TH, TP>(views[v].post, g - start[v], (int)threadIdx.x);
     }
 }
 
@@ -173,6 +183,14 @@ int post_items(const PostDesc &c, int stage) {
     return ceil_div(c.W, kPostTx) * ceil_div(c.H, kPostTy);
 }
 
+// Up to this many 64 x 8 strips (one and a half wavefronts per SIMD) a wavefront takes half a
+// strip: the chip is not full and a wavefront's own instructions are the time.  A half strip
+// interpolates 60 % of a strip's level rows, so that larger images take whole ones.  Composite
+// of 256x256 in float32 5.0 us by strips, 3.6 by halves, quarters gain nothing more (launches
+// bound bloom and tone mapping, 12.9 / 12.1 us); 1003x667 (1344 strips) 5.9 / 5.1; bloom and tone
+// mapping of 1280x720 (1800) 17.3 / 17.6 in half storage, 1920x1080 22.6 / 23.5.
+constexpr int kCompositeHalfStrips = 1536;
+
 template <typename TH, typename TP>
 static void launch_post(const PostDesc &c, bool level1_given, hipStream_t s) {
     if (c.nl >= 1) {
@@ -184,6 +202,10 @@ static void launch_post(const PostDesc &c, bool level1_given, hipStream_t s) {
         hipLaunchKernelGGL(k_bloom_blur<TP>, dim3(post_items(c, kStBloomBlur)), dim3(256), 0, s, c);
     }
     int tiles = post_items(c, kStComposite);
+    if (tiles <= kCompositeHalfStrips) {
+        hipLaunchKernelGGL((k_composite_halves<TH, TP>), dim3(2 * tiles), dim3(kPostTx), 0, s, c, 2 * tiles);
+        return;
+    }
     hipLaunchKernelGGL((k_composite<TH, TP>), dim3(tiles), dim3(kPostTx), 0, s, c, tiles);
 }
 

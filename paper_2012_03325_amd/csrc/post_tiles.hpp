@@ -259,13 +259,19 @@ __device__ __forceinline__ uint32_t encode8(float x, float exposure, float inv_g
 // bloom and tone mapping of 3840x2160 in half storage 63.8 -> 61.8 us, against
 // per-lane addresses, clamps of the 8-bit value and halves unpacked before the
 // difference.  1920x1080 in float32 (12.9 us, 45 MB) is bound by memory latency.
-template <int L>
+// (SR: the rows of the strip that a wavefront takes, all or a half.)
+template <int J0, int NJ>
+struct StripRows {
+    static constexpr int j0 = J0, n = NJ;
+};
+typedef StripRows<0, kPostTy> WholeStrip;
+template <int L, typename SR = WholeStrip>
 struct LevelRows {
     static constexpr int sh = L + 1, o = 1 - (1 << L), m = (1 << sh) - 1;
-    static constexpr int n = L == 1 ? 6 : L == 2 ? 4 : L == 3 ? 3 : 2;
     static constexpr float inv = 1.0f / (float)(1 << sh);
     // first row (relative to the strip's first footprint row) of pixel j
     static constexpr int rel(int j) { return L <= 3 ? ((2 * j + o) >> sh) - (o >> sh) : 0; }
+    static constexpr int first = rel(SR::j0), n = rel(SR::j0 + SR::n - 1) + 2 - first;
     // weight of pixel j (levels 1..3)
     static constexpr float wy(int j) { return (float)((2 * j + o) & m) * inv; }
 };
@@ -288,14 +294,14 @@ __device__ __forceinline__ float4 texel_difference(Half4 b, Half4 a) {
 
 // The level-L texels beside the thread's column on the rows under the strip, and
 // the column's weight.
-template <int L, typename TP>
+template <int L, typename SR, typename TP>
 struct LevelTexels {
-    TP a[LevelRows<L>::n], b[LevelRows<L>::n];
+    TP a[LevelRows<L, SR>::n], b[LevelRows<L, SR>::n];
     float wx;
 };
-template <int L, typename TP>
-__device__ __forceinline__ void load_level(const PostDesc &c, int x, int Y0, LevelTexels<L, TP> &t) {
-    using LR = LevelRows<L>;
+template <int L, typename SR, typename TP>
+__device__ __forceinline__ void load_level(const PostDesc &c, int x, int Y0, LevelTexels<L, SR, TP> &t) {
+    using LR = LevelRows<L, SR>;
     const int w = c.lw[L], h = c.lh[L];
     const TP *lvl = (const TP *)c.blur[L];
     int vx = 2 * x + LR::o;
@@ -303,7 +309,7 @@ __device__ __forceinline__ void load_level(const PostDesc &c, int x, int Y0, Lev
     int cx = vx >> LR::sh;
     unsigned c0 = (unsigned)min(max(cx, 0), w - 1), c1 = (unsigned)min(max(cx + 1, 0), w - 1);
     unsigned o0 = c0 * (unsigned)sizeof(TP), o1 = c1 * (unsigned)sizeof(TP);
-    int ay = (2 * Y0 + LR::o) >> LR::sh;
+    int ay = ((2 * Y0 + LR::o) >> LR::sh) + LR::first;
 #pragma unroll
     for (int r = 0; r < LR::n; ++r) {
         const TP *row = lvl + (unsigned)min(max(ay + r, 0), h - 1) * (unsigned)w;  // uniform: scalar arithmetic
@@ -313,10 +319,10 @@ __device__ __forceinline__ void load_level(const PostDesc &c, int x, int Y0, Lev
 }
 
 // Their values interpolated at the thread's column.
-template <int L, typename TP>
-__device__ __forceinline__ void level_rows(const LevelTexels<L, TP> &t, float (&rows)[LevelRows<L>::n][3]) {
+template <int L, typename SR, typename TP>
+__device__ __forceinline__ void level_rows(const LevelTexels<L, SR, TP> &t, float (&rows)[LevelRows<L, SR>::n][3]) {
 #pragma unroll
-    for (int r = 0; r < LevelRows<L>::n; ++r) {
+    for (int r = 0; r < LevelRows<L, SR>::n; ++r) {
         float4 a = unpack(t.a[r]), d = texel_difference(t.b[r], t.a[r]);
         rows[r][0] = fmaf(t.wx, d.x, a.x);
         rows[r][1] = fmaf(t.wx, d.y, a.y);
@@ -329,14 +335,14 @@ __device__ __forceinline__ void level_rows(const LevelTexels<L, TP> &t, float (&
 // w_L(j) = w_L(0) + 2 j / 2^(L+1); the two a_L are summed once per thread and
 // enter as the first addend, so a pixel spends one FMA per level and channel.
 // Absent levels contribute nothing (their difference and weight are 0).
-template <typename TP>
-__device__ __forceinline__ void init_coarse(const PostDesc &c, int Y0, const LevelTexels<4, TP> &t4,
-                                            const LevelTexels<5, TP> &t5, float (&acc)[kPostTy][3]) {
+template <typename SR, typename TP>
+__device__ __forceinline__ void init_coarse(const PostDesc &c, int Y0, const LevelTexels<4, SR, TP> &t4,
+                                            const LevelTexels<5, SR, TP> &t5, float (&acc)[SR::n][3]) {
     float base[3] = {0.0f, 0.0f, 0.0f}, d4[3] = {0.0f, 0.0f, 0.0f}, d5[3] = {0.0f, 0.0f, 0.0f};
     float w4 = 0.0f, w5 = 0.0f;
     if (c.nl >= 4) {
         float rows[2][3];
-        level_rows<4, TP>(t4, rows);
+        level_rows<4, SR, TP>(t4, rows);
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) {
             base[ch] = rows[0][ch];
@@ -346,7 +352,7 @@ __device__ __forceinline__ void init_coarse(const PostDesc &c, int Y0, const Lev
     }
     if (c.nl >= 5) {
         float rows[2][3];
-        level_rows<5, TP>(t5, rows);
+        level_rows<5, SR, TP>(t5, rows);
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) {
             base[ch] += rows[0][ch];
@@ -355,34 +361,34 @@ __device__ __forceinline__ void init_coarse(const PostDesc &c, int Y0, const Lev
         w5 = (float)((2 * Y0 + LevelRows<5>::o) & LevelRows<5>::m) * LevelRows<5>::inv;
     }
 #pragma unroll
-    for (int j = 0; j < kPostTy; ++j) {
-        float wj4 = w4 + (float)(2 * j) * LevelRows<4>::inv, wj5 = w5 + (float)(2 * j) * LevelRows<5>::inv;
+    for (int j = 0; j < SR::n; ++j) {
+        float wj4 = w4 + (float)(2 * (SR::j0 + j)) * LevelRows<4>::inv, wj5 = w5 + (float)(2 * (SR::j0 + j)) * LevelRows<5>::inv;
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) acc[j][ch] = fmaf(wj5, d5[ch], fmaf(wj4, d4[ch], base[ch]));
     }
 }
 
 // Levels 1..3: (1 - w) a + w b for the pixel's row pair, two FMAs per channel.
-template <int L, typename TP>
-__device__ __forceinline__ void add_fine(const LevelTexels<L, TP> &t, float (&acc)[kPostTy][3]) {
-    using LR = LevelRows<L>;
+template <int L, typename SR, typename TP>
+__device__ __forceinline__ void add_fine(const LevelTexels<L, SR, TP> &t, float (&acc)[SR::n][3]) {
+    using LR = LevelRows<L, SR>;
     float rows[LR::n][3];
-    level_rows<L, TP>(t, rows);
+    level_rows<L, SR, TP>(t, rows);
 #pragma unroll
-    for (int j = 0; j < kPostTy; ++j) {
-        const int r0 = LR::rel(j);
-        const float w = LR::wy(j);
+    for (int j = 0; j < SR::n; ++j) {
+        const int r0 = LR::rel(SR::j0 + j) - LR::first;
+        const float w = LR::wy(SR::j0 + j);
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) acc[j][ch] = fmaf(w, rows[r0 + 1][ch], fmaf(1.0f - w, rows[r0][ch], acc[j][ch]));
     }
 }
 
 // Bloom added to the strip's HDR, tone mapped and stored as RGBA8.
-template <bool kReinhard>
-__device__ __forceinline__ void store_strip(const PostDesc &c, int x, int Y0, const float (&px)[kPostTy][3],
-                                            const float (&acc)[kPostTy][3]) {
+template <bool kReinhard, int NJ>
+__device__ __forceinline__ void store_strip(const PostDesc &c, int x, int Y0, const float (&px)[NJ][3],
+                                            const float (&acc)[NJ][3]) {
 #pragma unroll
-    for (int j = 0; j < kPostTy; ++j) {
+    for (int j = 0; j < NJ; ++j) {
         if (Y0 + j >= c.H) break;
         float R = fmaf(c.strength, acc[j][0], px[j][0]);
         float G = fmaf(c.strength, acc[j][1], px[j][1]);
@@ -394,22 +400,23 @@ __device__ __forceinline__ void store_strip(const PostDesc &c, int x, int Y0, co
     }
 }
 
-// One 64 x 8 tile by one wavefront; `lane` is the thread's lane (its column).
-template <bool kOneTrip, typename TH, typename TP>
+// The rows SR of one 64 x 8 tile by one wavefront; `lane` is the thread's lane (its column).
+template <bool kOneTrip, typename SR, typename TH, typename TP>
 __device__ __forceinline__ void composite_tile(const PostDesc &c, int tile, int lane) {
     tile = __builtin_amdgcn_readfirstlane(tile);  // one per wavefront: rows are scalar addresses
     int tiles_x = (c.W + kPostTx - 1) / kPostTx;
     int ty = tile / tiles_x;
     int x = (tile - ty * tiles_x) * kPostTx + lane, Y0 = ty * kPostTy;
-    if (x >= c.W) return;
+    const int Y1 = Y0 + SR::j0;  // the first row of the part
+    if (x >= c.W || Y1 >= c.H) return;
     unsigned plane = (unsigned)c.W * (unsigned)c.H;
     const TH *hdr = (const TH *)c.hdr;
     // the strip's HDR first (in flight while the pyramid is read); rows below the image are
     // clamped to the last row and not stored
-    float px[kPostTy][3];
+    float px[SR::n][3];
 #pragma unroll
-    for (int j = 0; j < kPostTy; ++j) {
-        const TH *row = hdr + (unsigned)min(Y0 + j, c.H - 1) * (unsigned)c.W;
+    for (int j = 0; j < SR::n; ++j) {
+        const TH *row = hdr + (unsigned)min(Y1 + j, c.H - 1) * (unsigned)c.W;
         px[j][0] = ldf(row, (unsigned)x);
         px[j][1] = ldf(row + plane, (unsigned)x);
         px[j][2] = ldf(row + 2 * (size_t)plane, (unsigned)x);
@@ -422,31 +429,31 @@ __device__ __forceinline__ void composite_tile(const PostDesc &c, int tile, int 
     // mapping of 1920x1080 float 26.8 us against 26.3, of 3840x2160 half 61.8 against
     // 58.9; float texels in one trip need 140 registers (26.7);
     // float figures with unblurred levels of four floats.
-    float acc[kPostTy][3];
-    LevelTexels<4, TP> t4;
-    LevelTexels<5, TP> t5;
-    LevelTexels<1, TP> t1;
-    LevelTexels<2, TP> t2;
-    LevelTexels<3, TP> t3;
-    if (c.nl >= 5) load_level<5, TP>(c, x, Y0, t5);
-    if (c.nl >= 4) load_level<4, TP>(c, x, Y0, t4);
-    if (c.nl >= 1) load_level<1, TP>(c, x, Y0, t1);
+    float acc[SR::n][3];
+    LevelTexels<4, SR, TP> t4;
+    LevelTexels<5, SR, TP> t5;
+    LevelTexels<1, SR, TP> t1;
+    LevelTexels<2, SR, TP> t2;
+    LevelTexels<3, SR, TP> t3;
+    if (c.nl >= 5) load_level<5, SR, TP>(c, x, Y0, t5);
+    if (c.nl >= 4) load_level<4, SR, TP>(c, x, Y0, t4);
+    if (c.nl >= 1) load_level<1, SR, TP>(c, x, Y0, t1);
     if (kOneTrip) {
-        if (c.nl >= 2) load_level<2, TP>(c, x, Y0, t2);
-        if (c.nl >= 3) load_level<3, TP>(c, x, Y0, t3);
+        if (c.nl >= 2) load_level<2, SR, TP>(c, x, Y0, t2);
+        if (c.nl >= 3) load_level<3, SR, TP>(c, x, Y0, t3);
     }
     __builtin_amdgcn_sched_barrier(0);
-    init_coarse<TP>(c, Y0, t4, t5, acc);
-    if (c.nl >= 1) add_fine<1, TP>(t1, acc);
+    init_coarse<SR, TP>(c, Y0, t4, t5, acc);
+    if (c.nl >= 1) add_fine<1, SR, TP>(t1, acc);
     if (!kOneTrip) {
-        if (c.nl >= 2) load_level<2, TP>(c, x, Y0, t2);
-        if (c.nl >= 3) load_level<3, TP>(c, x, Y0, t3);
+        if (c.nl >= 2) load_level<2, SR, TP>(c, x, Y0, t2);
+        if (c.nl >= 3) load_level<3, SR, TP>(c, x, Y0, t3);
         __builtin_amdgcn_sched_barrier(0);
     }
-    if (c.nl >= 2) add_fine<2, TP>(t2, acc);
-    if (c.nl >= 3) add_fine<3, TP>(t3, acc);
-    if (c.tonemap == EPB_TONEMAP_REINHARD) store_strip<true>(c, x, Y0, px, acc);
-    else store_strip<false>(c, x, Y0, px, acc);
+    if (c.nl >= 2) add_fine<2, SR, TP>(t2, acc);
+    if (c.nl >= 3) add_fine<3, SR, TP>(t3, acc);
+    if (c.tonemap == EPB_TONEMAP_REINHARD) store_strip<true, SR::n>(c, x, Y1, px, acc);
+    else store_strip<false, SR::n>(c, x, Y1, px, acc);
 }
 
 }  // namespace epb
