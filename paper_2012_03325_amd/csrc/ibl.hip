@@ -246,63 +246,87 @@ __device__ __forceinline__ float4 mean_of_children(const float4 (&L)[4], const f
 }
 
 // Up to five chain levels in one launch: a block takes the 32 x 32 texels (or the
-// whole face) at its place of level `first` of all six faces and writes what it
-// covers of the levels below it, each from the one before in LDS.  The solid angles
-// of all its levels, which do not depend on the face, are made first, side by side
-// (level after level they are a serial chain: 17 us for the preparing launch of a
-// 6x64^2 cube).
+// whole face) at its place of level `first` of `faces` faces (all six, or one, see
+// chain_faces) and writes what it covers of the levels below it, each from the one
+// before in LDS.  The solid angles of all its levels, which do not depend on the
+// face, are made first, side by side (level after level they are a serial chain: 17 us
+// for the preparing launch of a 6x64^2 cube).
 constexpr int kChainStep = 5;
+// Faces a block takes where the chain step starts from faces of size S: one while that gives
+// few blocks, which the six faces' loads and the solid angles then bound (preparing launch of a
+// 6x64^2 cube 11.9 us with six, 8.5 with one; 6x256^2 12.2 / 11.7); six where the solid angles are
+// much of the work (6x512^2 26 / 34 us).
+__host__ __device__ inline int chain_faces(int S) { return S > 256 ? 6 : 1; }
 struct ChainLds {
     float4 a[6 * 16 * 16], b[6 * 8 * 8];
     float dw[32 * 32 + 16 * 16 + 8 * 8 + 4 * 4 + 2 * 2];
 };
 __device__ __forceinline__ void env_chain_block(int block, const float4 *__restrict__ env, float4 *__restrict__ chain,
-                                                int S, int first, int last, ChainLds &sm) {
+                                                int S, int first, int last, int faces, ChainLds &sm) {
     int Sp = S >> first;
     const float4 *src = first == 0 ? env : chain + chain_offset_pow2(S, first);
     int side = min(Sp, 32);  // a power of two
     int across = Sp / side;
-    int by = block / across, bx = block - by * across;
-    float4 *from = nullptr, *to = sm.a;
+    int group = block / (across * across), place = block - group * across * across;
+    int by = place / across, bx = place - by * across;
+    int f0 = group * faces;
     int t = (int)threadIdx.x;
-    int levels = min(kChainStep, last - first), total = 0;
-    for (int r = 0; r < levels; ++r) total += (side >> r) * (side >> r);
-    for (int q = t; q < total; q += 256) {
-        int r = 0, e = q;
-        while (e >= (side >> r) * (side >> r)) e -= (side >> r) * (side >> r), ++r;
-        int w = side >> r, y = e / w;
-        sm.dw[q] = texel_solid_angle(bx * w + (e - y * w), by * w + y, Sp >> r);
+    int levels = min(kChainStep, last - first);
+    int n = side >> 1;  // the first level's texels, at most one per thread
+    int ly = t / n, lx = t - ly * n;
+    bool live = t < n * n;
+    float *dws = sm.dw;  // of the level that the children are on
+    for (int r = 0, at = 0; r < levels; ++r) {
+        int w = side >> r;
+        for (int q = t; q < w * w; q += 256) {
+            int y = q / w;
+            dws[at + q] = texel_solid_angle(bx * w + (q - y * w), by * w + y, Sp >> r);
+        }
+        at += w * w;
     }
     __syncthreads();
-    const float *dws = sm.dw;  // of the level that the children are on
-    for (int k = first + 1; k <= min(first + kChainStep, last); ++k) {
-        int n = side >> (k - first), Sd = S >> k;  // this block's n x n texels of level k
+    if (live) {
+        int i = bx * n + lx, j = by * n + ly;
+        float4 *out = chain + chain_offset_pow2(S, first + 1);
+        float dw[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) dw[c] = dws[(2 * ly + (c >> 1)) * 2 * n + 2 * lx + (c & 1)];
+        for (int e = 0; e < faces; ++e) {
+            int f = f0 + e;
+            float4 L[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) L[c] = src[((size_t)f * Sp + 2 * j + (c >> 1)) * Sp + 2 * i + (c & 1)];
+            float4 v = mean_of_children(L, dw);
+            out[((size_t)f * (Sp >> 1) + j) * (Sp >> 1) + i] = v;
+            sm.a[(e * n + ly) * n + lx] = v;
+        }
+    }
+    __syncthreads();
+    float4 *from = sm.a, *to = sm.b;
+    for (int k = first + 2; k <= first + levels; ++k) {
+        dws += 4 * n * n;
+        n >>= 1;  // this block's n x n texels of level k
+        int Sd = S >> k;
         float4 *out = chain + chain_offset_pow2(S, k);
-        int each = from ? 1 : 6;  // faces per thread: all six where the children come from memory
-        for (int q = t; q < n * n * (6 / each); q += 256) {
-            int f0 = q / (n * n), r = q - f0 * n * n;
-            int ly = r / n, lx = r - ly * n;
-            int i = bx * n + lx, j = by * n + ly;
+        for (int q = t; q < n * n * faces; q += 256) {
+            int e = q / (n * n), r = q - e * n * n;
+            int y = r / n, x = r - y * n;
             float dw[4];
+            float4 L[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) dw[c] = dws[(2 * ly + (c >> 1)) * 2 * n + 2 * lx + (c & 1)];
-            for (int e = 0; e < each; ++e) {
-                int f = f0 + e;
-                float4 L[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    L[c] = from ? from[(f * 2 * n + 2 * ly + (c >> 1)) * 2 * n + 2 * lx + (c & 1)]
-                                : src[((size_t)f * Sp + 2 * j + (c >> 1)) * Sp + 2 * i + (c & 1)];
-                float4 v = mean_of_children(L, dw);
-                out[((size_t)f * Sd + j) * Sd + i] = v;
-                to[(f * n + ly) * n + lx] = v;
+            for (int c = 0; c < 4; ++c) {
+                dw[c] = dws[(2 * y + (c >> 1)) * 2 * n + 2 * x + (c & 1)];
+                L[c] = from[(e * 2 * n + 2 * y + (c >> 1)) * 2 * n + 2 * x + (c & 1)];
             }
+            float4 v = mean_of_children(L, dw);
+            out[((size_t)(f0 + e) * Sd + by * n + y) * Sd + bx * n + x] = v;
+            to[(e * n + y) * n + x] = v;
         }
         __syncthreads();
+        // (the next level's texels fit the other array: a quarter of them; it is read no more)
+        float4 *swap = from;
         from = to;
-        to = to == sm.a ? sm.b : sm.a;
-        dws += 4 * n * n;
-        // (the next level's texels fit the other array: 6 n^2 / 4 of them; it is read no more)
+        to = swap;
     }
 }
 
@@ -684,7 +708,7 @@ __global__ void __launch_bounds__(256) k_ibl_prepare(const IblArgs a) {
     if (b < a.env_blocks) {
         if constexpr (kFis) {
             __shared__ ChainLds sm;
-            env_chain_block(b, a.env, a.chain, a.S, 0, a.chain_last, sm);
+            env_chain_block(b, a.env, a.chain, a.S, 0, a.chain_last, chain_faces(a.S), sm);
         } else {
             env_rgb_block(b, a.env, a.S, a.rgb);
         }
@@ -706,7 +730,7 @@ __global__ void __launch_bounds__(256) k_ibl_prepare(const IblArgs a) {
 
 __global__ void __launch_bounds__(256) k_env_chain(const IblArgs a, int first) {
     __shared__ ChainLds sm;
-    env_chain_block((int)blockIdx.x, a.env, a.chain, a.S, first, a.chain_last, sm);
+    env_chain_block((int)blockIdx.x, a.env, a.chain, a.S, first, a.chain_last, chain_faces(a.S >> first), sm);
 }
 
 // Rounds of 8 heavy_run prefilter blocks and 8 light_run others: the two kinds are
@@ -867,7 +891,7 @@ hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr,
     }
     a.source_blocks = ceil_div(q.src * q.src * a.lpt, 256);
     int side = q.S < 32 ? q.S : 32;
-    if (q.fis) a.env_blocks = q.chain_last > 0 ? (q.S / side) * (q.S / side) : 0;
+    if (q.fis) a.env_blocks = q.chain_last > 0 ? (q.S / side) * (q.S / side) * (6 / chain_faces(q.S)) : 0;
     else a.env_blocks = q.pref_levels > 1 ? ceil_div(n0, 256) : 0;
     a.ggx_blocks = q.pref_levels > 1 ? ceil_div(q.pref_samples, 256) * q.pref_levels : 0;
     a.out_blocks = ceil_div(nout, 256);
@@ -889,7 +913,7 @@ hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr,
     else hipLaunchKernelGGL(k_ibl_prepare<false>, dim3(first), dim3(256), 0, s, a);
     for (int k = kChainStep; q.fis && k < q.chain_last; k += kChainStep) {
         int Sk = q.S >> k, w = Sk < 32 ? 1 : Sk / 32;
-        hipLaunchKernelGGL(k_env_chain, dim3(w * w), dim3(256), 0, s, a, k);
+        hipLaunchKernelGGL(k_env_chain, dim3(w * w * (6 / chain_faces(Sk))), dim3(256), 0, s, a, k);
     }
     if (q.fis) hipLaunchKernelGGL(k_ibl_integrate<true>, dim3(grid), dim3(256), lds, s, a);
     else hipLaunchKernelGGL(k_ibl_integrate<false>, dim3(grid), dim3(256), lds, s, a);
