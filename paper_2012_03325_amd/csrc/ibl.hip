@@ -4,8 +4,8 @@
 //
 // gfx950 mapping:
 //  * irradiance: 6*32^2 outputs x 6*64^2 source texels.  One thread per
-//    output, source texels staged through LDS in blocks of 256 and broadcast
-//    to all lanes; the source range is split across workgroups so that the
+//    output, source texels by scalar loads, those behind a wavefront's horizon
+//    left out; the source range is split across workgroups so that the
 //    grid gives every CU about four, and the per-split Kahan partials are combined in
 //    a fixed order by a second kernel (deterministic, no atomics).
 //  * a GGX sample's tangent-frame half vector depends on the sample and the
@@ -127,64 +127,126 @@ __device__ __forceinline__ void ibl_source_block(int block, const float4 *__rest
     }
 }
 
-// Partial irradiance sums over source chunk `chunk` for 256 outputs; `lds` holds
-// two blocks of 256 float4.
+// The value that lane k holds, in every lane.
+__device__ __forceinline__ float lane_value(float v, int k) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), k));
+}
+
+// Four texels by one scalar load.
+typedef float Float16 __attribute__((ext_vector_type(16), aligned(16)));
+typedef __attribute__((address_space(4))) const Float16 ConstFloat16;
+constexpr int kWaitScalar = 0xC07F;  // s_waitcnt: scalar loads and LDS only
+
+// Output o of the irradiance map for thread t of its launch: a wavefront takes an 8 x 8 tile of
+// a face where those fit (a narrow cone of normals, see below), 64 outputs in a row otherwise.
+__device__ __forceinline__ int irradiance_output(int t, int irr) {
+    if (irr & 7) return t;
+    int across = irr >> 3, lane = t & 63, tile = t >> 6;
+    int f = tile / (across * across), r = tile - f * across * across;
+    int ty = r / across, tx = r - ty * across;
+    return (f * irr + ty * 8 + (lane >> 3)) * irr + tx * 8 + (lane & 7);
+}
+
+// Partial irradiance sums over source chunk `chunk` for 256 outputs.  A group of four
+// source texels behind the horizon of every output of a wavefront adds exact zeros (to a
+// Kahan sum too) and is left out: each lane tests one group of 64 against the cone around
+// the wavefront's normals.  That is about a quarter of the groups for 16 x 16 outputs a
+// face and a third for 32 x 32.  The groups are the same for every lane and come by scalar
+// loads, the next one's in flight while one is added; vector issue bounds the sums.  With
+// every group, staged through LDS: whole precompute of 6x512^2 with 256 filtered samples
+// 130 us against 110, of 6x64^2 39.6 against 38.5 (16 x 16 outputs).
 // part layout: [chunk][output][8] = Kahan (s, c) of R, G, B, weight.
 __device__ __forceinline__ void irradiance_partial_block(int block, int chunk, const float4 *__restrict__ src,
                                                          const float4 *__restrict__ tab, int nsrc, int chunk_len,
-                                                         int irr, float *__restrict__ part, float4 *lds) {
-    float4 *sL = lds, *sT = lds + 256;
+                                                         int irr, float *__restrict__ part) {
     int nout = 6 * irr * irr;
-    int o = block * 256 + threadIdx.x;
-    v3 n = mk3(0, 0, 1);
-    if (o < nout) {
-        int f = o / (irr * irr), j = (o / irr) % irr, i = o % irr;
-        n = normalize(cube_texel_dir(f, i, j, irr));
+    int t = block * 256 + (int)threadIdx.x, lane = threadIdx.x & 63;
+    int o = irradiance_output(min(t, nout - 1), irr);
+    int f = o / (irr * irr), j = (o / irr) % irr, i = o % irr;
+    v3 n = normalize(cube_texel_dir(f, i, j, irr));
+    // The cone around a tile's normals: the axis through the tile's centre, the half angle h
+    // that of its farthest corner.  A direction d with axis . d below -sin h has n . d < 0 for all
+    // of them (by far more than rounding, with 1e-4 to spare).
+    float horizon = -2.0f;
+    v3 axis = n;
+    if (!(irr & 7)) {
+        auto corner = [&](int k) { return mk3(lane_value(n.x, k), lane_value(n.y, k), lane_value(n.z, k)); };
+        v3 c0 = corner(0), c1 = corner(7), c2 = corner(56), c3 = corner(63);
+        axis = normalize((c0 + c1) + (c2 + c3));
+        float ch = fminf(fminf(dot(c0, axis), dot(c1, axis)), fminf(dot(c2, axis), dot(c3, axis)));
+        if (ch > 0.1f) horizon = -sqrtf(fmaxf(0.0f, 1.0f - ch * ch)) - 1e-4f;
     }
     Kahan r{0, 0}, g{0, 0}, b{0, 0}, w{0, 0};
-    int beg = chunk * chunk_len;
-    int end = min(beg + chunk_len, nsrc);
-    for (int base = beg; base < end; base += 256) {
-        int t = base + threadIdx.x;
-        if (t < end) {
-            sL[threadIdx.x] = src[t];
-            sT[threadIdx.x] = tab[t];
-        }
-        __syncthreads();
-        int cnt = min(256, end - base);
-        // Every term is >= 0, so a group of four summed in plain float and then
-        // Kahan-added keeps the whole sum within about 3 units of rounding of
-        // its value (each group's error is bounded by its own terms), as with
-        // a Kahan add per term, at a quarter of the compensation work.
-        int q = 0;
-        for (; q + 4 <= cnt; q += 4) {
-            float c[4], lr[4], lg[4], lb[4];
+    int beg = min(chunk * chunk_len, nsrc), cnt = min(chunk_len, nsrc - beg), whole = cnt & ~3;  // (0: past the end)
+    src += beg;
+    tab += beg;
+    const ConstFloat16 *gs = (const ConstFloat16 *)as_constant((const float *)src);
+    const ConstFloat16 *gt = (const ConstFloat16 *)as_constant((const float *)tab);
+    // Every term is >= 0, so a group of four summed in plain float and then
+    // Kahan-added keeps the whole sum within about 3 units of rounding of
+    // its value (each group's error is bounded by its own terms), as with
+    // a Kahan add per term, at a quarter of the compensation work.
+    auto add = [&](const Float16 &l, const Float16 &T) {
+        float c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            c[u] = fmaxf(0.0f, fmaf(n.x, T[4 * u], fmaf(n.y, T[4 * u + 1], n.z * T[4 * u + 2]))) * T[4 * u + 3];
+        kahan_add(r, fmaf(l[12], c[3], fmaf(l[8], c[2], fmaf(l[4], c[1], l[0] * c[0]))));
+        kahan_add(g, fmaf(l[13], c[3], fmaf(l[9], c[2], fmaf(l[5], c[1], l[1] * c[0]))));
+        kahan_add(b, fmaf(l[14], c[3], fmaf(l[10], c[2], fmaf(l[6], c[1], l[2] * c[0]))));
+        kahan_add(w, ((c[0] + c[1]) + c[2]) + c[3]);
+    };
+    for (int base = 0; base < whole; base += 256) {
+        int first = base + 4 * lane;
+        bool need = false;
+        if (first < whole) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                float4 T = sT[q + u];
-                c[u] = fmaxf(0.0f, fmaf(n.x, T.x, fmaf(n.y, T.y, n.z * T.z))) * T.w;
-                float4 L = sL[q + u];
-                lr[u] = L.x;
-                lg[u] = L.y;
-                lb[u] = L.z;
+                float4 T = tab[first + u], L = src[first + u];
+                // (a texel that is no finite number reaches every output)
+                need |= !(dot(axis, mk3(T.x, T.y, T.z)) < horizon) || !(fabsf(L.x + L.y + L.z) < __builtin_inff());
             }
-            kahan_add(r, fmaf(lr[3], c[3], fmaf(lr[2], c[2], fmaf(lr[1], c[1], lr[0] * c[0]))));
-            kahan_add(g, fmaf(lg[3], c[3], fmaf(lg[2], c[2], fmaf(lg[1], c[1], lg[0] * c[0]))));
-            kahan_add(b, fmaf(lb[3], c[3], fmaf(lb[2], c[2], fmaf(lb[1], c[1], lb[0] * c[0]))));
-            kahan_add(w, ((c[0] + c[1]) + c[2]) + c[3]);
         }
-        for (; q < cnt; ++q) {
-            float4 T = sT[q];
-            float c = fmaxf(0.0f, fmaf(n.x, T.x, fmaf(n.y, T.y, n.z * T.z))) * T.w;
-            float4 L = sL[q];
-            kahan_add(r, L.x * c);
-            kahan_add(g, L.y * c);
-            kahan_add(b, L.z * c);
-            kahan_add(w, c);
+        unsigned long long todo = __ballot(need);
+        if (!todo) continue;
+        // the next group's scalar loads are in flight while one is added (at the end the last
+        // group's again)
+        int q = 0;
+        auto next = [&] {
+            if (todo) q = (base >> 2) + __builtin_ctzll(todo);
+            todo &= todo - 1;
+        };
+        int count = __builtin_popcountll(todo);
+        next();
+        Float16 l0 = gs[q], t0 = gt[q], l1, t1;
+        __builtin_amdgcn_s_waitcnt(kWaitScalar);
+        for (int pairs = count >> 1; pairs; --pairs) {
+            next();
+            l1 = gs[q];
+            t1 = gt[q];
+            __builtin_amdgcn_sched_barrier(0);
+            add(l0, t0);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(kWaitScalar);
+            next();
+            l0 = gs[q];
+            t0 = gt[q];
+            __builtin_amdgcn_sched_barrier(0);
+            add(l1, t1);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(kWaitScalar);
         }
-        __syncthreads();
+        if (count & 1) add(l0, t0);
     }
-    if (o < nout) {
+    for (int q = whole; q < cnt; ++q) {
+        float4 T = tab[q], L = src[q];
+        float c = fmaxf(0.0f, fmaf(n.x, T.x, fmaf(n.y, T.y, n.z * T.z))) * T.w;
+        kahan_add(r, L.x * c);
+        kahan_add(g, L.y * c);
+        kahan_add(b, L.z * c);
+        kahan_add(w, c);
+    }
+    if (t < nout) {
         float *p = part + ((size_t)chunk * nout + o) * 8;
         p[0] = r.s; p[1] = g.s; p[2] = b.s; p[3] = w.s;
         p[4] = r.c; p[5] = g.c; p[6] = b.c; p[7] = w.c;
@@ -734,7 +796,11 @@ __global__ void __launch_bounds__(256) k_env_chain(const IblArgs a, int first) {
 }
 
 // Rounds of 8 heavy_run prefilter blocks and 8 light_run others: the two kinds are
-// spread evenly over the launch, and every index keeps its XCD (blockIdx % 8).
+// spread over the launch, and every index keeps its XCD (blockIdx % 8).  The kind that
+// would hold up the other issues first: the plain prefilter waits for the texture data
+// path, so that the others, which only compute, go ahead of it (348 us for 6x512^2, 351
+// without); the filtered prefilter's wavefronts are chains of dependent lookups, and go
+// ahead in longer runs (6x512^2, 1024 samples: 217 us; in runs of 8 without, 238).
 template <bool kFis>
 __global__ void __launch_bounds__(256) k_ibl_integrate(const IblArgs a) {
     extern __shared__ float4 lds[];
@@ -745,11 +811,13 @@ __global__ void __launch_bounds__(256) k_ibl_integrate(const IblArgs a) {
         for (int m = 0; m < a.levels; ++m) {
             const IblLevel &v = a.level[m];
             if (b < v.blocks) {
-                if constexpr (kFis)
+                if constexpr (kFis) {
+                    __builtin_amdgcn_s_setprio(1);
                     prefilter_fis_block(b, a.env, a.chain, a.S, a.chain_last, v.sm, v.table, a.pref_samples, v.chunks,
                                         v.part);
-                else
+                } else {
                     prefilter_block(b, v.blocks, a.rgb, a.S, v.sm, v.table, a.pref_samples, v.out);
+                }
                 return;
             }
             b -= v.blocks;
@@ -757,10 +825,11 @@ __global__ void __launch_bounds__(256) k_ibl_integrate(const IblArgs a) {
         return;
     }
     int b = round * kNumXcd * a.light_run + at - kNumXcd * a.heavy_run;
+    if constexpr (!kFis) __builtin_amdgcn_s_setprio(1);
     if (b < a.partial_blocks) {
         int c = b / a.out_blocks;
         return irradiance_partial_block(b - c * a.out_blocks, c, a.src_tex, a.src_tab, 6 * a.src * a.src, a.chunk_len,
-                                        a.irr, a.part, lds);
+                                        a.irr, a.part);
     }
     b -= a.partial_blocks;
     if (b < a.lut_blocks) brdf_lut_rows_block(b, a.lut, a.lut_samples, a.lut_out, (float2 *)lds);
@@ -899,14 +968,13 @@ hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr,
     bool lut_rows = q.lut_samples <= kLutLdsSamples;
     a.lut_blocks = lut_rows ? q.lut * ceil_div(q.lut, kLutRowSlice) : 0;
     a.light = a.partial_blocks + a.lut_blocks;
-    // rounds of 8 prefilter blocks per XCD, the others spread over them
-    a.heavy_run = a.heavy > 0 ? 8 : 0;
+    // rounds of so many prefilter blocks per XCD, the others spread over them (k_ibl_integrate)
+    a.heavy_run = a.heavy > 0 ? (q.fis ? 32 : 8) : 0;
     int rounds = a.heavy > 0 ? ceil_div(a.heavy, kNumXcd * a.heavy_run) : 1;
     a.light_run = ceil_div(a.light, kNumXcd * rounds);
     int grid = rounds * kNumXcd * (a.heavy_run + a.light_run);
     // (at most 16 KB: ten workgroups would fit a CU, more than the prefilter's registers allow)
-    size_t lds = 2 * 256 * sizeof(float4);
-    if (lut_rows && (size_t)q.lut_samples * sizeof(float2) > lds) lds = (size_t)q.lut_samples * sizeof(float2);
+    size_t lds = lut_rows ? (size_t)q.lut_samples * sizeof(float2) : 0;
 
     int first = a.source_blocks + a.env_blocks + a.ggx_blocks + mirror_blocks;
     if (q.fis) hipLaunchKernelGGL(k_ibl_prepare<true>, dim3(first), dim3(256), 0, s, a);
