@@ -26,7 +26,7 @@
 // Bound: double-precision issue and the latency of the candidate loop where
 // spheres overlap, the G-buffer's stores elsewhere.  Measured per call (512
 // spheres and the plane): 1920x1080 G-buffer 27 us (74.6 MB of stores, 2.8 TB/s),
-// 2048^2 depth map 27 us; 16384 spheres at 1280x720 48 us.  One workgroup per
+// 2048^2 depth map 23 us; 16384 spheres at 1280x720 48 us.  One workgroup per
 // 16x16 pixels that took every box by itself, its list to every pixel and an
 // XCD-contiguous order: 50, 57 and 163 us.
 #include "device_common.hpp"
@@ -127,11 +127,31 @@ __global__ void __launch_bounds__(64 * NX *NY) k_raycast(const RayScene s, const
     if (t == 0) list_n = 0;
     // (the region's far edges at most 16384 + a region: 16 bits hold every sum)
     Short2 at_x = {(short)-(X0 + kRx), (short)X0}, at_y = {(short)-(Y0 + kRy), (short)Y0};
+    // The view-space rays' x of the region's columns and y of its rows: one division each where
+    // a lane has several pixels (four 2048^2 depth maps and their tiling 144 us with the divisions
+    // of every pixel, 139), every lane's own elsewhere (720p, 16384 spheres: 40.7 us against 41.1,
+    // the additional barrier delays the region test).
+    double v0, v1s[PPT];
+    if constexpr (PPT > 1) {
+        __shared__ double ray_v[kRx + kRy];
+        static_assert(kRx + kRy <= kThreads, "a thread per column and row");
+        if (t < kRx + kRy) {
+            bool col = t < kRx;
+            double at = col ? (double)(X0 + t) + 0.5 - c.cx : (double)(Y0 + t - kRx) + 0.5 - c.cy;
+            double v = at / (col ? c.fx : c.fy);
+            ray_v[t] = col ? v : -v;
+        }
+        __syncthreads();
+        v0 = ray_v[x - X0];
+        for (int j = 0; j < PPT; ++j) v1s[j] = ray_v[kRx + y - Y0 + j * kRayLy];
+    } else {
+        v0 = ((double)x + 0.5 - c.cx) / c.fx;
+        v1s[0] = -(((double)y + 0.5 - c.cy) / c.fy);
+    }
     double d[PPT][3], aa[PPT];
-    double v0 = ((double)x + 0.5 - c.cx) / c.fx;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-        double v1 = -(((double)(y + j * kRayLy) + 0.5 - c.cy) / c.fy), v2 = -1.0;
+        double v1 = v1s[j], v2 = -1.0;
         for (int k = 0; k < 3; ++k) d[j][k] = c.M[k] * v0 + c.M[4 + k] * v1 + c.M[8 + k] * v2;
         aa[j] = d[j][0] * d[j][0] + d[j][1] * d[j][1] + d[j][2] * d[j][2];
     }
@@ -169,7 +189,7 @@ __global__ void __launch_bounds__(64 * NX *NY) k_raycast(const RayScene s, const
         best[j] = far_num[j] = __builtin_inf();
         who[j] = -1;
     }
-    __syncthreads();
+    if (PPT == 1) __syncthreads();  // list_n (with several pixels the barrier above)
     for (int base = 0; base < s.n; base += kGroup) {
         // the spheres of this group whose boxes meet the region, appended in any order
         Short2 bx[kLoads], by[kLoads];
