@@ -205,7 +205,7 @@ int check_post_params(const epb_post_params *params) {
 }
 
 int build_post(const void *hdr, epb_dtype hdr_dtype, int32_t width, int32_t height, const epb_post_params *params,
-               uint8_t *ldr_out, void *scratch, size_t scratch_bytes, epb::PostDesc *out) {
+               uint8_t *ldr_out, void *scratch, size_t scratch_bytes, epb::PostDesc *out, bool in_batch = false) {
     if (!hdr || !params || !ldr_out) return EPB_ERR_NULL;
     if (width < 1 || height < 1 || width > EPB_MAX_IMAGE_SIZE || height > EPB_MAX_IMAGE_SIZE) return EPB_ERR_SIZE;
     if (!valid_dtype(hdr_dtype)) return EPB_ERR_DTYPE;
@@ -216,7 +216,7 @@ int build_post(const void *hdr, epb_dtype hdr_dtype, int32_t width, int32_t heig
     if (!scratch || scratch_bytes < plan.bytes) return EPB_ERR_SCRATCH;
     if (!aligned16(scratch)) return EPB_ERR_ALIGN;
     *out = epb::post_desc(plan, hdr, params->threshold, params->strength, params->exposure, params->gamma,
-                          params->tonemap, ldr_out, scratch);
+                          params->tonemap, ldr_out, scratch, in_batch);
     return EPB_OK;
 }
 
@@ -594,7 +594,8 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
                               v.hdr_dtype, &a)))
             return st;
         d.shade = epb::shade_desc(a);
-        if ((st = build_post(hdr, v.hdr_dtype, v.cam.width, v.cam.height, v.post, v.ldr, s_post, vs.post, &d.post)))
+        if ((st = build_post(hdr, v.hdr_dtype, v.cam.width, v.cam.height, v.post, v.ldr, s_post, vs.post, &d.post,
+                             true)))
             return st;
         if (q.fuse_bloom && d.post.nl >= 1) {  // the shading stage writes bloom level 1
             d.shade.bloom1 = d.post.raw[1];

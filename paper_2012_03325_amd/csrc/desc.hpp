@@ -149,7 +149,8 @@ struct RayOut {
 constexpr int kSsaoPrepW = 256;           // half-resolution texels per prep item
 constexpr int kBlurTx = 16, kBlurTy = 8;  // SSAO blur tile
 constexpr int kPostTx = 64, kPostTy = 8;  // composite: one wavefront, a column of 8 pixels per thread
-constexpr int kBloomTx = 32, kBloomTy = 16;  // bloom-blur tile
+constexpr int kBloomTx = 60;  // bloom blur: columns of a wavefront
+constexpr int kBloomRows = 4, kBloomBatchRows = 8;  // its rows, in a single view and in a batch
 constexpr int kDownTile = 16;             // bloom_down: 16x16 level-1 texels (32x32 pixels)
 
 // Selectable shapes (the schedule picks one per stage).

@@ -107,7 +107,7 @@ struct PostPlan {
 };
 PostPlan post_plan(int W, int H, int levels, epb_dtype pyr_dtype);
 PostDesc post_desc(const PostPlan &q, const void *hdr, float threshold, float strength, float exposure,
-                   float gamma, int tonemap, uint8_t *ldr, void *scratch);
+                   float gamma, int tonemap, uint8_t *ldr, void *scratch, bool in_batch);
 int post_items(const PostDesc &c, int stage);
 // level1_given: the shading pass has written pyramid level 1 (the fused form)
 hipError_t launch_bloom_tonemap(const PostDesc &c, epb_dtype hdr_dtype, epb_dtype pyr_dtype, hipStream_t s,

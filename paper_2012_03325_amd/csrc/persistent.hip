@@ -39,7 +39,6 @@ union PersistLds {
         float sa[blur_lds_rows<kPersistSsaoT, kPersistSsaoT>()][kPersistSsaoT + 3];
     } blur;
     DownLds down;
-    BlurLds bloom;
 };
 
 __device__ __forceinline__ int *persist_done(PersistState *st) { return reinterpret_cast<int *>(st + 1); }
@@ -66,7 +65,7 @@ __device__ __forceinline__ void persist_tile(const BatchHeader *h, const ViewDes
     case kStBlur: ssao_blur_tile<kPersistSsaoT, kPersistSsaoT, T>(d.ssao, t, sm.blur.sd, sm.blur.sa); break;
     case kStShade: shade_tile<32, 8, false, false, T, T, T>(d.shade, t); break;
     case kStDown: bloom_down_tile<T, TP>(d.post, t, sm.down); break;
-    case kStBloomBlur: bloom_blur_item<TP>(d.post, t, sm.bloom); break;
+    case kStBloomBlur: bloom_blur_item<kBloomBatchRows, TP>(d.post, t); break;
     default: {
         int tiles = ((d.post.W + kPostTx - 1) / kPostTx) * ((d.post.H + kPostTy - 1) / kPostTy);
         int tile = t * kPersistCompositeTiles + (int)(threadIdx.x / kPostTx);

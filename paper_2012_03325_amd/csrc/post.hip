@@ -7,9 +7,9 @@
 //    forms the bright map and its 2x2 means, and builds pyramid levels 1..5 of
 //    that tile in LDS (16x16 level-1 texels halve down to one at level 5),
 //    writing every level once.
-//  * bloom_blur: all levels in one launch; each workgroup stages the 36x20
-//    texel footprint of its 32x16 tile in LDS and applies the separable
-//    [1 4 6 4 1] / 16 binomial (clamp to edge) horizontally then vertically.
+//  * bloom_blur: all levels in one launch; a wavefront holds its tile's columns
+//    in registers and applies the separable [1 4 6 4 1] / 16 binomial (clamp to
+//    edge) horizontally across lanes, then vertically.
 //  * composite: a wavefront covers 64 columns x 8 rows, a thread one column
 //    of 8 pixels; every blurred level is interpolated at the column (rows
 //    first, then between two rows per pixel) in registers; each thread adds
@@ -42,8 +42,7 @@ __global__ void __launch_bounds__(256) k_bloom_down_from1(const PostDesc c, int 
 
 template <typename TP>
 __global__ void __launch_bounds__(256) k_bloom_blur(const PostDesc c) {
-    __shared__ BlurLds sm;
-    bloom_blur_item<TP>(c, blockIdx.x, sm);
+    bloom_blur_item<kBloomRows, TP>(c, blockIdx.x);
 }
 
 template <typename TH, typename TP>
@@ -90,7 +89,6 @@ __global__ void __launch_bounds__(256) k_bloom_down_from1_batch(const void *__re
 
 template <typename TP>
 __global__ void __launch_bounds__(256) k_bloom_blur_batch(const void *__restrict__ table) {
-    __shared__ BlurLds sm;
     const BatchHeader *h = (const BatchHeader *)table;
     const int *start = batch_start(table, kStBloomBlur);
     const ViewDesc *views = batch_views(table);
@@ -98,7 +96,7 @@ __global__ void __launch_bounds__(256) k_bloom_blur_batch(const void *__restrict
     for (int it = w.lb; it < w.count; it += w.stride) {
         int g = w.first + it;
         int v = find_view(start, h->n_views, g);
-        bloom_blur_item<TP>(views[v].post, g - start[v], sm);
+        bloom_blur_item<kBloomBatchRows, TP>(views[v].post, g - start[v]);
     }
 }
 
@@ -146,7 +144,7 @@ PostPlan post_plan(int W, int H, int levels, epb_dtype pyr_dtype) {
 }
 
 PostDesc post_desc(const PostPlan &q, const void *hdr, float threshold, float strength, float exposure,
-                   float gamma, int tonemap, uint8_t *ldr, void *scratch) {
+                   float gamma, int tonemap, uint8_t *ldr, void *scratch, bool in_batch) {
     PostDesc c{};
     c.W = q.W;
     c.H = q.H;
@@ -164,7 +162,7 @@ PostDesc post_desc(const PostPlan &q, const void *hdr, float threshold, float st
     int nb = 0;
     for (int l = 1; l <= c.nl; ++l) {
         c.blk_start[l] = nb;
-        nb += ceil_div(c.lw[l], kBloomTx) * ceil_div(c.lh[l], kBloomTy);
+        nb += ceil_div(c.lw[l], kBloomTx) * ceil_div(c.lh[l], 4 * (in_batch ? kBloomBatchRows : kBloomRows));
     }
     c.blk_start[c.nl + 1] = nb;
     c.threshold = threshold;
