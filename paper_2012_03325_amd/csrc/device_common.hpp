@@ -296,6 +296,14 @@ __device__ __forceinline__ float stored_as(float v, const __half *) {
     return __half2float(__float2half_rn(fminf(v, 65504.0f)));
 }
 
+// v of the lane before and after (lanes 0 and 63 get 0).
+__device__ __forceinline__ float lane_before(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lane_after(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xF, 0xF, true));
+}
+
 // Bright-pass weight max(Y - threshold, 0) / Y of a pixel (Rec. 709 luminance
 // Y), with a reciprocal; a luminance below the smallest normal float blooms
 // nothing (its reciprocal would overflow).

@@ -167,13 +167,6 @@ __device__ __forceinline__ PackedRgb binomial5(PackedRgb a, PackedRgb b, PackedR
                (a.z + e.z + 4.0f * (b.z + d.z) + 6.0f * m.z) * 0.0625f};
 }
 
-// v of the lane before and after (lanes 0 and 63 get 0).
-__device__ __forceinline__ float lane_before(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xF, 0xF, true));
-}
-__device__ __forceinline__ float lane_after(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xF, 0xF, true));
-}
 __device__ __forceinline__ PackedRgb lane_before(PackedRgb v) {
     return PackedRgb{lane_before(v.x), lane_before(v.y), lane_before(v.z)};
 }

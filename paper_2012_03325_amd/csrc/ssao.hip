@@ -28,7 +28,8 @@
 //    64 samples) whose range check makes an out-of-image element read 0 (the
 //    sample is discarded by its range test).
 //  * blur: 4x4 bilateral mean; the 19x11 depth/AO footprint of a 16x8 tile is
-//    staged through LDS.
+//    staged through LDS; in a batch a wavefront holds columns of its footprint
+//    in registers and exchanges them across lanes.
 //  * raw and blur in one kernel for small images (see ssao_fused_tile).
 //  * every stage has a single-view kernel (one block per tile, XCD-aware
 //    order) and a batched kernel that walks the tiles of many views.
@@ -109,9 +110,7 @@ __global__ void __launch_bounds__(kSsaoLdsTile *kSsaoLdsTile) k_ssao_raw_batch_l
 }
 
 template <typename TA>
-__global__ void __launch_bounds__(kBlurTx *kBlurTy) k_ssao_blur_batch(const void *__restrict__ table) {
-    __shared__ float sd[blur_lds_rows<kBlurTx, kBlurTy>()][kBlurTx + 3];
-    __shared__ float sa[blur_lds_rows<kBlurTx, kBlurTy>()][kBlurTx + 3];
+__global__ void __launch_bounds__(256) k_ssao_blur_batch(const void *__restrict__ table) {
     const BatchHeader *h = (const BatchHeader *)table;
     const int *start = batch_start(table, kStBlur);
     const ViewDesc *views = batch_views(table);
@@ -119,7 +118,7 @@ __global__ void __launch_bounds__(kBlurTx *kBlurTy) k_ssao_blur_batch(const void
     for (int it = w.lb; it < w.count; it += w.stride) {
         int g = w.first + it;
         int v = find_view(start, h->n_views, g);
-        ssao_blur_tile<kBlurTx, kBlurTy, TA>(views[v].ssao, g - start[v], sd, sa);
+        ssao_blur_columns<kBlurRows, TA>(views[v].ssao, g - start[v]);
     }
 }
 
@@ -152,6 +151,7 @@ SsaoPlan ssao_plan(int W, int H) {
     return q;
 }
 
+// (of a batch)
 int ssao_items(const SsaoDesc &c, int stage, int ssao_tile) {
     switch (stage) {
     case kStPrep: return c.Hh * ceil_div(c.Wh, kSsaoPrepW);
@@ -159,7 +159,7 @@ int ssao_items(const SsaoDesc &c, int stage, int ssao_tile) {
         TileShape t = kSsaoTiles[ssao_tile];
         return ceil_div(c.Wh, t.tx) * ceil_div(c.Hh, t.ty);
     }
-    default: return ceil_div(c.Wh, kBlurTx) * ceil_div(c.Hh, kBlurTy);
+    default: return ceil_div(c.Wh, kBlurCols) * ceil_div(c.Hh, 4 * kBlurRows);
     }
 }
 
@@ -264,7 +264,7 @@ hipError_t launch_ssao(const SsaoDesc &c, epb_dtype gdtype, epb_dtype ao_dtype, 
         else go_raw<16, 8, 8, __half, __half>(c, s);
     }
     if (c.blur) {
-        int tiles = ssao_items(c, kStBlur, 0);
+        int tiles = ceil_div(c.Wh, kBlurTx) * ceil_div(c.Hh, kBlurTy);
         if (ao_dtype == EPB_F32)
             hipLaunchKernelGGL(k_ssao_blur<float>, dim3(tiles), dim3(kBlurTx * kBlurTy), 0, s, c, tiles);
         else
@@ -350,9 +350,9 @@ hipError_t launch_ssao_batch(const BatchHeader &h, const void *table, hipStream_
     if (h.blur) {
         int grid = batch_grid(h.total[kStBlur], h.blocks_per_cu);
         if (h.ao_dtype == EPB_F32)
-            hipLaunchKernelGGL(k_ssao_blur_batch<float>, dim3(grid), dim3(kBlurTx * kBlurTy), 0, s, table);
+            hipLaunchKernelGGL(k_ssao_blur_batch<float>, dim3(grid), dim3(256), 0, s, table);
         else
-            hipLaunchKernelGGL(k_ssao_blur_batch<__half>, dim3(grid), dim3(kBlurTx * kBlurTy), 0, s, table);
+            hipLaunchKernelGGL(k_ssao_blur_batch<__half>, dim3(grid), dim3(256), 0, s, table);
     }
     return hipGetLastError();
 }
