@@ -205,7 +205,8 @@ int check_post_params(const epb_post_params *params) {
 }
 
 int build_post(const void *hdr, epb_dtype hdr_dtype, int32_t width, int32_t height, const epb_post_params *params,
-               uint8_t *ldr_out, void *scratch, size_t scratch_bytes, epb::PostDesc *out, bool in_batch = false) {
+               uint8_t *ldr_out, void *scratch, size_t scratch_bytes, epb::PostDesc *out,
+               epb::BlurShape blur = epb::kBloomSingle) {
     if (!hdr || !params || !ldr_out) return EPB_ERR_NULL;
     if (width < 1 || height < 1 || width > EPB_MAX_IMAGE_SIZE || height > EPB_MAX_IMAGE_SIZE) return EPB_ERR_SIZE;
     if (!valid_dtype(hdr_dtype)) return EPB_ERR_DTYPE;
@@ -216,7 +217,7 @@ int build_post(const void *hdr, epb_dtype hdr_dtype, int32_t width, int32_t heig
     if (!scratch || scratch_bytes < plan.bytes) return EPB_ERR_SCRATCH;
     if (!aligned16(scratch)) return EPB_ERR_ALIGN;
     *out = epb::post_desc(plan, hdr, params->threshold, params->strength, params->exposure, params->gamma,
-                          params->tonemap, ldr_out, scratch, in_batch);
+                          params->tonemap, ldr_out, scratch, blur);
     return EPB_OK;
 }
 
@@ -575,6 +576,8 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
     long long total[epb::kStages] = {}, chunks[epb::kStages] = {};
     int *start = (int *)((char *)table + epb::batch_start_offset());
     int *cstart = (int *)((char *)table + epb::batch_cstart_offset(n_views));
+    int *columns = (int *)((char *)table + epb::batch_columns_offset(n_views));
+    epb::BatchHeader h{};
     for (int i = 0; i < n_views; ++i) {
         const epb_view &v = views[i];
         ViewScratch vs;
@@ -595,7 +598,7 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
             return st;
         d.shade = epb::shade_desc(a);
         if ((st = build_post(hdr, v.hdr_dtype, v.cam.width, v.cam.height, v.post, v.ldr, s_post, vs.post, &d.post,
-                             true)))
+                             q.persistent ? epb::kBloomTile : epb::kBloomBatch)))
             return st;
         if (q.fuse_bloom && d.post.nl >= 1) {  // the shading stage writes bloom level 1
             d.shade.bloom1 = d.post.raw[1];
@@ -611,7 +614,7 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
             items[epb::kStBlur] = d.ssao.blur ? epb::ssao_items(d.ssao, epb::kStBlur, q.ssao_tile) : 0;
             items[epb::kStShade] = epb::shade_items(d.shade, q.shade_tile);
             items[epb::kStDown] = epb::post_items(d.post, epb::kStDown);
-            items[epb::kStBloomBlur] = epb::post_items(d.post, epb::kStBloomBlur);
+            items[epb::kStBloomBlur] = epb::bloom_blur_tiles(d.post);
             items[epb::kStComposite] = epb::post_items(d.post, epb::kStComposite);
         }
         for (int k = 0; k < epb::kStages; ++k) {
@@ -622,9 +625,18 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
             cstart[k * (n_views + 1) + i] = (int)chunks[k];
             chunks[k] += nc;
         }
+        // (at most as many as the stages' tiles, so they fit as well; none in a persistent launch)
+        int cols[epb::kColumnStages] = {};
+        if (!q.persistent) {
+            cols[epb::kColSsao] = d.ssao.blur ? epb::ssao_blur_column_items(d.ssao) : 0;
+            cols[epb::kColBloom] = epb::post_items(d.post, epb::kStBloomBlur);
+        }
+        for (int k = 0; k < epb::kColumnStages; ++k) {
+            columns[k * (n_views + 1) + i] = h.columns[k];
+            h.columns[k] += cols[k];
+        }
         std::memcpy(&vd[i], &d, sizeof(d));
     }
-    epb::BatchHeader h{};
     h.magic = epb::kBatchMagic;
     h.n_views = n_views;
     h.gdtype = v0.gbuf.dtype;
@@ -643,6 +655,7 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
         start[k * (n_views + 1) + n_views] = (int)total[k];
         cstart[k * (n_views + 1) + n_views] = (int)chunks[k];
     }
+    for (int k = 0; k < epb::kColumnStages; ++k) columns[k * (n_views + 1) + n_views] = h.columns[k];
     h.compact = compact;
     h.persistent = q.persistent ? 1 : 0;
     h.chunk = q.persistent;

@@ -149,8 +149,12 @@ struct RayOut {
 constexpr int kSsaoPrepW = 256;           // half-resolution texels per prep item
 constexpr int kBlurTx = 16, kBlurTy = 8;  // SSAO blur tile
 constexpr int kPostTx = 64, kPostTy = 8;  // composite: one wavefront, a column of 8 pixels per thread
-constexpr int kBloomTx = 60;  // bloom blur: columns of a wavefront
-constexpr int kBloomRows = 4, kBloomBatchRows = 8;  // its rows, in a single view and in a batch
+// Bloom blur: an item is four wavefronts' columns and rows, by the launch that walks it (the
+// persistent one's tiles are also the blur stage's count of work items).
+struct BlurShape {
+    int cols, rows;
+};
+constexpr BlurShape kBloomSingle = {60, 4}, kBloomBatch = {60, 8}, kBloomTile = {32, 4};
 constexpr int kDownTile = 16;             // bloom_down: 16x16 level-1 texels (32x32 pixels)
 
 // Selectable shapes (the schedule picks one per stage).
@@ -167,9 +171,10 @@ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // ---------------------------------------------------------------------------
 // batch table: [BatchHeader][int start[kStages][n + 1]][int cstart[kStages][n + 1]]
-// [pad to 16][ViewDesc[n]][pad to 256][PersistState][int done[n][kStages]]
+// [int columns[kColumnStages][n + 1]][pad to 16][ViewDesc[n]][pad to 256][PersistState][int done[n][kStages]]
 // ---------------------------------------------------------------------------
 enum Stage { kStPrep = 0, kStRaw, kStBlur, kStShade, kStDown, kStBloomBlur, kStComposite, kStages };
+enum ColumnStage { kColSsao = 0, kColBloom, kColumnStages };
 
 struct ViewDesc {
     SsaoDesc ssao;
@@ -193,6 +198,7 @@ struct BatchHeader {
     int total_chunks;
     int chunk_first[kStages + 1];   // first chunk of each stage
     int compact;                    // some view takes a compact depth copy (else its stage is not launched)
+    int columns[kColumnStages];     // items of the blur kernels, which take columns instead of the stages' tiles
 };
 
 // Work counters of the persistent launch, in the device copy of the table; the
@@ -219,8 +225,11 @@ __host__ __device__ inline size_t batch_start_offset() { return align_up(sizeof(
 __host__ __device__ inline size_t batch_cstart_offset(int n) {
     return batch_start_offset() + sizeof(int) * kStages * (size_t)(n + 1);
 }
+__host__ __device__ inline size_t batch_columns_offset(int n) {
+    return batch_cstart_offset(n) + sizeof(int) * kStages * (size_t)(n + 1);
+}
 __host__ __device__ inline size_t batch_views_offset(int n) {
-    return align_up(batch_cstart_offset(n) + sizeof(int) * kStages * (size_t)(n + 1), 16);
+    return align_up(batch_columns_offset(n) + sizeof(int) * kColumnStages * (size_t)(n + 1), 16);
 }
 __host__ __device__ inline size_t batch_state_offset(int n) {
     return align_up(batch_views_offset(n) + sizeof(ViewDesc) * (size_t)n, 256);
@@ -236,6 +245,11 @@ __host__ __device__ inline const int *batch_start(const void *table, int stage) 
 __host__ __device__ inline const int *batch_cstart(const void *table, int stage) {
     const BatchHeader *h = (const BatchHeader *)table;
     return (const int *)((const char *)table + batch_cstart_offset(h->n_views)) + stage * (h->n_views + 1);
+}
+// First item of every view in a blur kernel's walk, as batch_start.
+__host__ __device__ inline const int *batch_columns(const void *table, int k) {
+    const BatchHeader *h = (const BatchHeader *)table;
+    return (const int *)((const char *)table + batch_columns_offset(h->n_views)) + k * (h->n_views + 1);
 }
 __host__ __device__ inline const ViewDesc *batch_views(const void *table) {
     const BatchHeader *h = (const BatchHeader *)table;

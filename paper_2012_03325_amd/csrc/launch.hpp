@@ -49,6 +49,7 @@ SsaoDesc ssao_desc(const SsaoPlan &q, const float *depth, const void *normal, co
                    float tau, int blur, void *ao_out, void *scratch,
                    bool in_batch);
 int ssao_items(const SsaoDesc &c, int stage, int ssao_tile);
+int ssao_blur_column_items(const SsaoDesc &c);
 hipError_t launch_ssao(const SsaoDesc &c, epb_dtype gdtype, epb_dtype ao_dtype, hipStream_t s);
 hipError_t launch_ssao_batch(const BatchHeader &h, const void *table, hipStream_t s);
 // Device address of the library's own SSAO scratch array on the current device
@@ -107,7 +108,8 @@ struct PostPlan {
 };
 PostPlan post_plan(int W, int H, int levels, epb_dtype pyr_dtype);
 PostDesc post_desc(const PostPlan &q, const void *hdr, float threshold, float strength, float exposure,
-                   float gamma, int tonemap, uint8_t *ldr, void *scratch, bool in_batch);
+                   float gamma, int tonemap, uint8_t *ldr, void *scratch, BlurShape blur);
+int bloom_blur_tiles(const PostDesc &c);
 int post_items(const PostDesc &c, int stage);
 // level1_given: the shading pass has written pyramid level 1 (the fused form)
 hipError_t launch_bloom_tonemap(const PostDesc &c, epb_dtype hdr_dtype, epb_dtype pyr_dtype, hipStream_t s,

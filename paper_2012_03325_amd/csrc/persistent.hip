@@ -65,7 +65,7 @@ __device__ __forceinline__ void persist_tile(const BatchHeader *h, const ViewDes
     case kStBlur: ssao_blur_tile<kPersistSsaoT, kPersistSsaoT, T>(d.ssao, t, sm.blur.sd, sm.blur.sa); break;
     case kStShade: shade_tile<32, 8, false, false, T, T, T>(d.shade, t); break;
     case kStDown: bloom_down_tile<T, TP>(d.post, t, sm.down); break;
-    case kStBloomBlur: bloom_blur_item<kBloomBatchRows, TP>(d.post, t); break;
+    case kStBloomBlur: bloom_blur_item<kBloomTile.cols, kBloomTile.rows, TP>(d.post, t); break;
     default: {
         int tiles = ((d.post.W + kPostTx - 1) / kPostTx) * ((d.post.H + kPostTy - 1) / kPostTy);
         int tile = t * kPersistCompositeTiles + (int)(threadIdx.x / kPostTx);

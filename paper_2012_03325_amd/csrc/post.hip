@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(256) k_bloom_down_from1(const PostDesc c, int 
 
 template <typename TP>
 __global__ void __launch_bounds__(256) k_bloom_blur(const PostDesc c) {
-    bloom_blur_item<kBloomRows, TP>(c, blockIdx.x);
+    bloom_blur_item<kBloomSingle.cols, kBloomSingle.rows, TP>(c, blockIdx.x);
 }
 
 template <typename TH, typename TP>
@@ -90,13 +90,13 @@ __global__ void __launch_bounds__(256) k_bloom_down_from1_batch(const void *__re
 template <typename TP>
 __global__ void __launch_bounds__(256) k_bloom_blur_batch(const void *__restrict__ table) {
     const BatchHeader *h = (const BatchHeader *)table;
-    const int *start = batch_start(table, kStBloomBlur);
+    const int *start = batch_columns(table, kColBloom);
     const ViewDesc *views = batch_views(table);
-    XcdRange w = xcd_range(h->total[kStBloomBlur]);
+    XcdRange w = xcd_range(h->columns[kColBloom]);
     for (int it = w.lb; it < w.count; it += w.stride) {
         int g = w.first + it;
         int v = find_view(start, h->n_views, g);
-        bloom_blur_item<kBloomBatchRows, TP>(views[v].post, g - start[v]);
+        bloom_blur_item<kBloomBatch.cols, kBloomBatch.rows, TP>(views[v].post, g - start[v]);
     }
 }
 
@@ -144,7 +144,7 @@ PostPlan post_plan(int W, int H, int levels, epb_dtype pyr_dtype) {
 }
 
 PostDesc post_desc(const PostPlan &q, const void *hdr, float threshold, float strength, float exposure,
-                   float gamma, int tonemap, uint8_t *ldr, void *scratch, bool in_batch) {
+                   float gamma, int tonemap, uint8_t *ldr, void *scratch, BlurShape blur) {
     PostDesc c{};
     c.W = q.W;
     c.H = q.H;
@@ -162,7 +162,7 @@ PostDesc post_desc(const PostPlan &q, const void *hdr, float threshold, float st
     int nb = 0;
     for (int l = 1; l <= c.nl; ++l) {
         c.blk_start[l] = nb;
-        nb += ceil_div(c.lw[l], kBloomTx) * ceil_div(c.lh[l], 4 * (in_batch ? kBloomBatchRows : kBloomRows));
+        nb += ceil_div(c.lw[l], blur.cols) * ceil_div(c.lh[l], 4 * blur.rows);
     }
     c.blk_start[c.nl + 1] = nb;
     c.threshold = threshold;
@@ -173,6 +173,13 @@ PostDesc post_desc(const PostPlan &q, const void *hdr, float threshold, float st
     c.hdr = hdr;
     c.ldr = (uint32_t *)ldr;
     return c;
+}
+
+// Tiles of 32 x 16 texels of all levels, the blur stage's work items in a batch table.
+int bloom_blur_tiles(const PostDesc &c) {
+    int n = 0;
+    for (int l = 1; l <= c.nl; ++l) n += ceil_div(c.lw[l], kBloomTile.cols) * ceil_div(c.lh[l], 4 * kBloomTile.rows);
+    return n;
 }
 
 int post_items(const PostDesc &c, int stage) {
@@ -215,8 +222,8 @@ static void launch_post_batch_t(const BatchHeader &h, const void *table, hipStre
     else if (h.total[kStDown] > 0)
         hipLaunchKernelGGL((k_bloom_down_batch<TH, TP>), dim3(batch_grid(h.total[kStDown], h.blocks_per_cu)),
                            dim3(256), 0, s, table);
-    if (h.total[kStBloomBlur] > 0)
-        hipLaunchKernelGGL(k_bloom_blur_batch<TP>, dim3(batch_grid(h.total[kStBloomBlur], h.blocks_per_cu)),
+    if (h.columns[kColBloom] > 0)
+        hipLaunchKernelGGL(k_bloom_blur_batch<TP>, dim3(batch_grid(h.columns[kColBloom], h.blocks_per_cu)),
                            dim3(256), 0, s, table);
     hipLaunchKernelGGL((k_composite_batch<TH, TP>), dim3(batch_grid(h.total[kStComposite], h.blocks_per_cu)),
                        dim3(kPostTx), 0, s, table);

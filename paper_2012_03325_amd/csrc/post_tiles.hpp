@@ -159,7 +159,7 @@ __device__ __forceinline__ void bloom_down_from1_tile(const PostDesc &c, int til
 }
 
 // ---------------------------------------------------------------------------
-// bloom_blur: 60 columns of one level by four wavefronts
+// bloom_blur: columns of one level by four wavefronts
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ PackedRgb binomial5(PackedRgb a, PackedRgb b, PackedRgb m, PackedRgb d, PackedRgb e) {
     return PackedRgb{(a.x + e.x + 4.0f * (b.x + d.x) + 6.0f * m.x) * 0.0625f,
@@ -175,23 +175,24 @@ __device__ __forceinline__ PackedRgb lane_after(PackedRgb v) {
 }
 
 // An item is four wavefronts' tiles below each other, each of kRows rows.  A wavefront's lanes
-// are 64 columns, two on each side the halo: a lane holds its column of the footprint in
-// registers, the horizontal sums take their neighbours from other lanes.  No LDS and no barriers,
-// and all rows are in flight together.  Four rows in a single view (latency: 1920x1080 in float32
-// 6.4 us, with eight rows 6.6, 256x256 3.6 and 4.6), eight in a batch (a quarter instead of half of
-// the rows read twice: 16 views of 13.2 Mpx in half storage 17.3 us against 19.4).  Tiles of 32 x 16
-// staged through LDS with both sums there: 7.8, 3.8 and 24.3 us.
-template <int kRows, typename TP>
+// are kCols columns and two on each side for the halo: a lane holds its column of the footprint
+// in registers, the horizontal sums take their neighbours from other lanes.  No LDS and no
+// barriers, and all rows are in flight together.  Four rows in a single view (latency: 1920x1080
+// in float32 6.4 us, with eight rows 6.6, 256x256 3.6 and 4.6), eight in a batch (a quarter instead
+// of half of the rows read twice: 16 views of 13.2 Mpx in half storage 17.3 us against 19.4).  Tiles
+// of 32 x 16 staged through LDS with both sums there: 7.8, 3.8 and 24.3 us.
+template <int kCols, int kRows, typename TP>
 __device__ __forceinline__ void bloom_blur_item(const PostDesc &c, int item) {
+    static_assert(kCols <= 60, "and a halo of two on each side");
     typedef typename RawTexel<TP>::type TR;
     int L = 1;
     while (L < c.nl && item >= c.blk_start[L + 1]) ++L;
     int local = item - c.blk_start[L];
     int w = c.lw[L], h = c.lh[L];
-    int tx = (w + kBloomTx - 1) / kBloomTx;
+    int tx = (w + kCols - 1) / kCols;
     int ty = local / tx;
     int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    int X = (local - ty * tx) * kBloomTx - 2 + lane, Y0 = (ty * 4 + wave) * kRows;
+    int X = (local - ty * tx) * kCols - 2 + lane, Y0 = (ty * 4 + wave) * kRows;
     if (Y0 >= h) return;
     const TR *src = (const TR *)c.raw[L];
     unsigned col = (unsigned)min(max(X, 0), w - 1) * (unsigned)sizeof(TR);
@@ -200,7 +201,7 @@ __device__ __forceinline__ void bloom_blur_item(const PostDesc &c, int item) {
     for (int r = 0; r < kRows + 4; ++r)
         v[r] = ldo(src + (unsigned)min(max(Y0 + r - 2, 0), h - 1) * (unsigned)w, col);
     __builtin_amdgcn_sched_barrier(0);
-    bool store = lane >= 2 && lane < 2 + kBloomTx && X < w;
+    bool store = lane >= 2 && lane < 2 + kCols && X < w;
     PackedRgb s[kRows + 4];
 #pragma unroll
     for (int r = 0; r < kRows + 4; ++r) {

@@ -112,9 +112,9 @@ __global__ void __launch_bounds__(kSsaoLdsTile *kSsaoLdsTile) k_ssao_raw_batch_l
 template <typename TA>
 __global__ void __launch_bounds__(256) k_ssao_blur_batch(const void *__restrict__ table) {
     const BatchHeader *h = (const BatchHeader *)table;
-    const int *start = batch_start(table, kStBlur);
+    const int *start = batch_columns(table, kColSsao);
     const ViewDesc *views = batch_views(table);
-    XcdRange w = xcd_range(h->total[kStBlur]);
+    XcdRange w = xcd_range(h->columns[kColSsao]);
     for (int it = w.lb; it < w.count; it += w.stride) {
         int g = w.first + it;
         int v = find_view(start, h->n_views, g);
@@ -151,7 +151,6 @@ SsaoPlan ssao_plan(int W, int H) {
     return q;
 }
 
-// (of a batch)
 int ssao_items(const SsaoDesc &c, int stage, int ssao_tile) {
     switch (stage) {
     case kStPrep: return c.Hh * ceil_div(c.Wh, kSsaoPrepW);
@@ -159,9 +158,11 @@ int ssao_items(const SsaoDesc &c, int stage, int ssao_tile) {
         TileShape t = kSsaoTiles[ssao_tile];
         return ceil_div(c.Wh, t.tx) * ceil_div(c.Hh, t.ty);
     }
-    default: return ceil_div(c.Wh, kBlurCols) * ceil_div(c.Hh, 4 * kBlurRows);
+    default: return ceil_div(c.Wh, kBlurTx) * ceil_div(c.Hh, kBlurTy);
     }
 }
+
+int ssao_blur_column_items(const SsaoDesc &c) { return ceil_div(c.Wh, kBlurCols) * ceil_div(c.Hh, 4 * kBlurRows); }
 
 SsaoDesc ssao_desc(const SsaoPlan &q, const float *depth, const void *normal, const HostCam &cam, const float *kernel,
                    int n_samples, const float *noise, float radius, float bias, float tau, int blur, void *ao_out,
@@ -264,7 +265,7 @@ hipError_t launch_ssao(const SsaoDesc &c, epb_dtype gdtype, epb_dtype ao_dtype, 
         else go_raw<16, 8, 8, __half, __half>(c, s);
     }
     if (c.blur) {
-        int tiles = ceil_div(c.Wh, kBlurTx) * ceil_div(c.Hh, kBlurTy);
+        int tiles = ssao_items(c, kStBlur, 0);
         if (ao_dtype == EPB_F32)
             hipLaunchKernelGGL(k_ssao_blur<float>, dim3(tiles), dim3(kBlurTx * kBlurTy), 0, s, c, tiles);
         else
@@ -348,7 +349,7 @@ hipError_t launch_ssao_batch(const BatchHeader &h, const void *table, hipStream_
         else pick_raw_batch<__half, __half>(h, table, s);
     }
     if (h.blur) {
-        int grid = batch_grid(h.total[kStBlur], h.blocks_per_cu);
+        int grid = batch_grid(h.columns[kColSsao], h.blocks_per_cu);
         if (h.ao_dtype == EPB_F32)
             hipLaunchKernelGGL(k_ssao_blur_batch<float>, dim3(grid), dim3(256), 0, s, table);
         else
