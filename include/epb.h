@@ -369,7 +369,8 @@ int epb_bloom_tonemap(const void *hdr, epb_dtype hdr_dtype, int32_t width, int32
  * level 1 of the bloom pyramid (Sec. 5.3) formed in the shading pass: each
  * 2x2 block of shaded pixels is bright-passed and averaged from the HDR values
  * as stored while they are still in registers, so the bloom pass does not read
- * the HDR image back to build it.  Arguments are those of the two calls (the
+ * the HDR image back to build it (up to 3 * 2^20 pixels; the two calls' own
+ * kernels are faster above).  Arguments are those of the two calls (the
  * bloom pass takes W, H from cam and its HDR input is hdr_out); the same
  * validation and statuses.  hdr_out, ldr_out and scratch hold bitwise what
  * epb_shade then epb_bloom_tonemap leave there.
@@ -381,8 +382,9 @@ int epb_shade_post(const epb_gbuffer *gbuf, const epb_camera *cam, const void *a
 
 /* ------------------------------------------------------------------------
  * Batched form: the whole pass (SSAO, shading, bloom and tone mapping) of many
- * views of any sizes with one launch per stage (seven launches per batch, not
- * seven per view), or all of it in one persistent launch (epb_schedule).  Every stage walks the work items (tiles) of all views, so
+ * views of any sizes with one launch per stage (up to seven launches per batch,
+ * not per view), or all of it in one persistent launch (epb_schedule).  Every
+ * stage walks the work items (tiles) of all views, so
  * small views do not leave the device idle and a batch is a fixed sequence of
  * launches that can be captured in a HIP graph and replayed.
  *
@@ -430,7 +432,7 @@ typedef struct {
                               launch: as many as fit); k in 1..64: a grid of k
                               workgroups per compute unit that loops over the
                               work                                             */
-    int32_t persistent;    /* 0: one launch per stage (seven per batch);
+    int32_t persistent;    /* 0: one launch per stage (up to seven);
                               k in 1..EPB_MAX_PERSISTENT_CHUNK: the whole batch
                               in one launch whose work items are k tiles of one
                               view and stage (requires one storage type for

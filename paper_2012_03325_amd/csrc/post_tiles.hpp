@@ -258,7 +258,7 @@ __device__ __forceinline__ uint32_t encode8(float x, float exposure, float inv_g
 // composite (81 % busy, half storage): 16 views of 13.2 Mpx 57 -> 52.5 us, and
 // bloom and tone mapping of 3840x2160 in half storage 63.8 -> 61.8 us, against
 // per-lane addresses, clamps of the 8-bit value and halves unpacked before the
-// difference.  1920x1080 in float32 (12.9 us, 45 MB) is bound by memory latency.
+// difference.  1920x1080 in float32 (11.2 us, 45 MB) is bound by memory latency.
 // (SR: the rows of the strip that a wavefront takes, all or a half.)
 template <int J0, int NJ>
 struct StripRows {

@@ -199,7 +199,7 @@ __device__ __forceinline__ void shade_pixel(const ShadeDesc &c, int x, int y, fl
             }
         }
         // ambient inputs after the light loop: gathered before it, their taps would stay live
-        // through the loop (123 VGPRs, 4 waves/SIMD); here the kernel needs 65 (7 waves/SIMD)
+        // through the loop (123 VGPRs, 4 waves/SIMD); here the kernel needs 63 to 65 (8 or 7 waves/SIMD)
         float2 AB = lut_bilinear(c.lut, c.lut_dims, NoV, r);
         float4 E = cube_bilinear(c.irr, c.irr_dims, n);
         v3 Rf = n * (2.0f * nv_raw) - V;
