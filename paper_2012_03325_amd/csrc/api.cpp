@@ -9,6 +9,7 @@
 
 #include "../../include/epb.h"
 #include "launch.hpp"
+#include "tile_order.hpp"
 
 namespace {
 
@@ -573,7 +574,7 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
     epb::ViewDesc *vd = (epb::ViewDesc *)((char *)table + epb::batch_views_offset(n_views));
     char *sc = (char *)scratch;
     int compact = 0;
-    long long total[epb::kStages] = {}, chunks[epb::kStages] = {};
+    long long total[epb::kStages] = {}, chunks[epb::kStages] = {}, largest = 0;  // (shading tiles of a view)
     int *start = (int *)((char *)table + epb::batch_start_offset());
     int *cstart = (int *)((char *)table + epb::batch_cstart_offset(n_views));
     int *columns = (int *)((char *)table + epb::batch_columns_offset(n_views));
@@ -617,6 +618,7 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
             items[epb::kStBloomBlur] = epb::bloom_blur_tiles(d.post);
             items[epb::kStComposite] = epb::post_items(d.post, epb::kStComposite);
         }
+        if (items[epb::kStShade] > largest) largest = items[epb::kStShade];
         for (int k = 0; k < epb::kStages; ++k) {
             if (total[k] + items[k] > 0x7fffffffLL) return EPB_ERR_SIZE;
             start[k * (n_views + 1) + i] = (int)total[k];
@@ -657,6 +659,7 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
     }
     for (int k = 0; k < epb::kColumnStages; ++k) columns[k * (n_views + 1) + n_views] = h.columns[k];
     h.compact = compact;
+    h.shade_chunks = epb::shade_in_chunks(largest, n_views, total[epb::kStShade]) ? 1 : 0;
     h.persistent = q.persistent ? 1 : 0;
     h.chunk = q.persistent;
     h.gate = q.wait_limit < 0 ? 0 : 1;

@@ -1,7 +1,7 @@
 // Device-side helpers shared by the gfx950 kernels of the shading pass:
 // small vector algebra, storage conversions, camera projection, cube-map
-// addressing and filtering, compensated summation and the XCD-aware block
-// order.  Nothing here is host code.
+// addressing and filtering, compensated summation and the batched kernels' walk
+// over their items.  Nothing here is host code.
 #pragma once
 
 #include <hip/hip_fp16.h>
@@ -9,11 +9,11 @@
 #include <stdint.h>
 
 #include "desc.hpp"
+#include "tile_order.hpp"
 
 namespace epb {
 
 constexpr float kPi = 3.14159265358979323846f;
-constexpr int kNumXcd = 8;  // MI355X: 256 CUs in 8 accelerator complex dies
 
 // ---------------------------------------------------------------------------
 // storage
@@ -341,20 +341,9 @@ __device__ __forceinline__ float add_row_pair(float v) {
     return __builtin_bit_cast(float, even) + __builtin_bit_cast(float, odd);
 }
 
-// ---------------------------------------------------------------------------
-// launch order: consecutive tiles go to the same XCD (own L2)
-// ---------------------------------------------------------------------------
-// The dispatcher hands workgroup b to XCD b % 8.  Remap so that XCD k
-// processes a contiguous range of tiles (a bijection for any grid size).
-__device__ __forceinline__ int xcd_tile(int b, int nb) {
-    int q = nb / kNumXcd, r = nb % kNumXcd;
-    int x = b % kNumXcd, local = b / kNumXcd;
-    return x < r ? x * (q + 1) + local : r * (q + 1) + (x - r) * q + local;
-}
-
 // Work distribution of persistent (or one-item-per-block) grids: XCD x (the
 // blocks b with b mod 8 == x) owns a contiguous share of the items, visited by
-// its blocks in turn.  With one block per item this is the bijection above.
+// its blocks in turn.  With one block per item this is xcd_tile's bijection.
 // The trip count depends on blockIdx only, so loops may contain barriers.
 struct XcdRange {
     int first, count, lb, stride;
@@ -362,30 +351,13 @@ struct XcdRange {
 __device__ __forceinline__ XcdRange xcd_range(int total) {
     int nb = gridDim.x, b = blockIdx.x;
     int x = b % kNumXcd;
-    int q = total / kNumXcd, r = total % kNumXcd;
+    XcdShare own = xcd_share(x, total);
     XcdRange w;
-    w.first = x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q;
-    w.count = q + (x < r ? 1 : 0);
+    w.first = own.first;
+    w.count = own.count;
     w.stride = nb / kNumXcd + (x < nb % kNumXcd ? 1 : 0);
     w.lb = b / kNumXcd;
     return w;
-}
-
-// The shading pass's order: chunks of kShadeChunk consecutive items go to the XCDs
-// in turn, so that every XCD gets its share of the costly rows (a contiguous
-// eighth of the image leaves the XCDs of the sky idle) while neighbouring tiles
-// still share an L2; what does not fill a round of chunks is split as above.
-// Item `it` of XCD x (0 <= it < xcd_chunk_count):
-constexpr int kShadeChunk = 64;
-__device__ __forceinline__ int xcd_chunk_item(int x, int it, int total) {
-    int rounds = total / (kNumXcd * kShadeChunk);
-    if (it < rounds * kShadeChunk) return (it / kShadeChunk * kNumXcd + x) * kShadeChunk + it % kShadeChunk;
-    int first = rounds * (kNumXcd * kShadeChunk), rest = total - first;
-    int q = rest / kNumXcd, r = rest % kNumXcd;
-    return first + x * q + min(x, r) + (it - rounds * kShadeChunk);
-}
-__device__ __forceinline__ int xcd_chunk_count(int x, int total) {
-    return total / kNumXcd + (x < total % kNumXcd ? 1 : 0);
 }
 
 // View owning work item g: start[v] <= g < start[v + 1] (binary search; uniform).

@@ -14,7 +14,8 @@
 // 128 measure alike).  At that order the kernel is bound by VALU issue and the
 // texture data path together: 8 waves per SIMD, the shadow patches of all lights
 // fetched ahead of the light loop, or the G-buffer fetched ahead of the depth
-// test gain nothing more.  Lights travel in the kernel
+// test gain nothing more.  Batches of about equal views go by contiguous shares instead
+// (see shade_in_chunks).  Lights travel in the kernel
 // argument segment and are read with scalar loads.
 //
 // Float32 care where the reference is float64:
@@ -54,9 +55,10 @@ k_shade_batch(const void *__restrict__ table) {
     const int *start = batch_start(table, kStShade);
     const ViewDesc *views = batch_views(table);
     int total = h->total[kStShade], x = (int)blockIdx.x % kNumXcd;
-    int count = xcd_chunk_count(x, total), stride = (int)gridDim.x / kNumXcd + (x < (int)gridDim.x % kNumXcd ? 1 : 0);
-    for (int it = (int)blockIdx.x / kNumXcd; it < count; it += stride) {
-        int g = xcd_chunk_item(x, it, total);
+    bool chunks = h->shade_chunks;
+    XcdRange w = xcd_range(total);
+    for (int it = w.lb; it < w.count; it += w.stride) {
+        int g = chunks ? xcd_chunk_item(x, it, total) : w.first + it;
         int v = find_view(start, h->n_views, g);
         shade_tile<TX, TY, kBloom1, false, TG, TA, TH>(views[v].shade, g - start[v]);
     }

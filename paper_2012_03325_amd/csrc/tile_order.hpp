@@ -1,0 +1,50 @@
+// Launch order: which work items the workgroups of each XCD take.  The dispatcher
+// hands workgroup b to XCD b % 8, and each XCD has its own L2, so consecutive items
+// should go to the same XCD; but items of an image cost unequally (sky, ground), so
+// every XCD also has to get its share of the costly ones.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace epb {
+
+constexpr int kNumXcd = 8;  // MI355X: 256 CUs in 8 accelerator complex dies
+
+// XCD x's contiguous share of `total` items: with one workgroup per item a bijection
+// for any total.  A batch of views of about one size takes it in every stage: an
+// XCD gets whole views, or runs of views, and with them the cheap and the costly parts.
+struct XcdShare {
+    int first, count;
+};
+__host__ __device__ inline XcdShare xcd_share(int x, int total) {
+    int q = total / kNumXcd, r = total % kNumXcd;
+    return XcdShare{x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q, q + (x < r ? 1 : 0)};
+}
+
+// The same as the item of workgroup b of nb.
+__host__ __device__ inline int xcd_tile(int b, int nb) { return xcd_share(b % kNumXcd, nb).first + b / kNumXcd; }
+
+// The shading pass's order for one view, and for a batch of uneven views: chunks of
+// kShadeChunk consecutive tiles go to the XCDs in turn, so that every XCD gets its share
+// of the costly rows (a contiguous eighth of the image leaves the XCDs of the sky
+// idle) while neighbouring tiles still share an L2; what does not fill a round of
+// chunks is split as above.
+// Tile `it` of XCD x (0 <= it < xcd_share(x, total).count):
+constexpr int kShadeChunk = 64;
+__host__ __device__ inline int xcd_chunk_item(int x, int it, int total) {
+    int rounds = total / (kNumXcd * kShadeChunk);
+    if (it < rounds * kShadeChunk) return (it / kShadeChunk * kNumXcd + x) * kShadeChunk + it % kShadeChunk;
+    int first = rounds * (kNumXcd * kShadeChunk);
+    return first + xcd_share(x, total - first).first + (it - rounds * kShadeChunk);
+}
+
+// Whether a batch's shading takes that order (largest: tiles of its largest view).  Not with
+// views of about one size: a round of chunks is 512 tiles, so that views of 256 or 512 tiles
+// give an XCD the same part of every view (256 views of 256x256 in half storage 397 us, float32
+// 451; 316 and 371 by contiguous shares; 8 of 320x240 45.4 / 41.8).  With a view of more than
+// twice the mean a contiguous share is mostly a part of that view (13 views of up to 1920x1080 in
+// float32 431 us, 422 in chunks; 16 in half storage 359 / 355; at 2.1 times the mean one or
+// the other is ahead by 1 or 2 %).
+inline bool shade_in_chunks(long long largest, int n_views, long long total) { return largest * n_views > 2 * total; }
+
+}  // namespace epb

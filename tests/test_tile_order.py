@@ -1,0 +1,82 @@
+"""The kernels' launch order, compiled for the host: every item goes to one XCD
+once, and no XCD gets a one-sided share of what the items are part of."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2012_03325_amd import epb as E
+from tests.test_abi import _Batch
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2012_03325_amd", "csrc")
+
+# prints the XCD of every item: in contiguous shares, or in the shading pass's chunks
+PROBE = r"""
+#include "tile_order.hpp"
+#include <cstdio>
+#include <cstdlib>
+int main(int argc, char **argv) {
+    bool chunked = std::atoi(argv[1]) != 0;
+    int total = std::atoi(argv[2]);
+    unsigned char *owner = (unsigned char *)std::malloc(total);
+    for (int i = 0; i < total; ++i) owner[i] = 255;
+    for (int x = 0; x < epb::kNumXcd; ++x) {
+        epb::XcdShare s = epb::xcd_share(x, total);
+        for (int it = 0; it < s.count; ++it) {
+            int g = chunked ? epb::xcd_chunk_item(x, it, total) : s.first + it;
+            if (g < 0 || g >= total || owner[g] != 255) return 1;
+            owner[g] = (unsigned char)x;
+        }
+    }
+    return std::fwrite(owner, 1, total, stdout) == (size_t)total ? 0 : 2;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def owners(tmp_path_factory):
+    d = tmp_path_factory.mktemp("order")
+    (d / "probe.cpp").write_text(PROBE)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", CSRC, "-I", "/opt/rocm/include",
+                    str(d / "probe.cpp"), "-o", str(d / "probe")], check=True)
+
+    def run(chunked, total):
+        r = subprocess.run([str(d / "probe"), str(int(chunked)), str(total)], capture_output=True)
+        assert r.returncode == 0, f"an item twice, never or out of range ({total} items)"
+        return np.frombuffer(r.stdout, np.uint8)
+    return run
+
+
+@pytest.mark.parametrize("total", [1, 7, 8, 63, 64, 65, 511, 512, 513, 1023, 1024, 1031, 1535, 1536, 8100, 65537])
+def test_every_item_once(owners, total):
+    for chunked in (0, 1):
+        o = owners(chunked, total)
+        assert (o < 8).all()
+        counts = np.bincount(o, minlength=8)
+        assert counts.max() - counts.min() <= 1
+
+
+@pytest.mark.parametrize("views", [5, 12, 32, 64, 256])
+@pytest.mark.parametrize("tiles", [64, 128, 192, 256, 320, 510, 512, 576, 1024])
+def test_batch_of_equal_views(owners, views, tiles):
+    """Every XCD takes each tile of the view about equally often (a contiguous share of L items
+    holds a position of a view of T tiles floor(L / T) or ceil(L / T) times)."""
+    o = owners(0, views * tiles).reshape(views, tiles)
+    per = np.stack([(o == x).sum(0) for x in range(8)])
+    assert per.max() - per.min() <= 1
+
+
+# views of one size, of sizes within twice the mean, and uneven ones
+@pytest.mark.parametrize("sizes,chunks", [([(256, 256)] * 16, 0), ([(320, 240)] * 8, 0), ([(64, 48)], 0),
+                                          ([(64, 64)] * 3 + [(128, 64)] * 3, 0), ([(256, 256)] * 8 + [(512, 512)], 1),
+                                          ([(1920, 1080), (1280, 720), (640, 480), (320, 240)] * 3, 1)])
+def test_order_of_a_batch(sizes, chunks):
+    """The shading stage's order in the table's header: contiguous shares, which the test above
+    needs for equal views, unless one view has more than twice the mean's tiles."""
+    b = _Batch(sizes)
+    assert b.build() == E.EPB_OK
+    words = list(C.cast(b.table, C.POINTER(C.c_int32 * 37)).contents)
+    assert words[36] == chunks
