@@ -28,12 +28,20 @@ __host__ __device__ inline int xcd_tile(int b, int nb) { return xcd_share(b % kN
 // kShadeChunk consecutive tiles go to the XCDs in turn, so that every XCD gets its share
 // of the costly rows (a contiguous eighth of the image leaves the XCDs of the sky
 // idle) while neighbouring tiles still share an L2; what does not fill a round of
-// chunks is split as above.
+// chunks is split as above.  An XCD's chunk moves on by one every second round and every
+// eighth: at one place in every round, an image whose rows fill 512 tiles a whole number of
+// times (4096 pixels wide, 8192, 16384) would give an XCD the same columns all the way down
+// (4096x1024 with only sky in its right half: 74 us so, 52 with the shift, 53 with contiguous
+// shares).  A larger shift changes images of two rounds, which have nothing to gain
+// (512x512 in half storage 10.0 us, with one a round 10.4).
 // Tile `it` of XCD x (0 <= it < xcd_share(x, total).count):
 constexpr int kShadeChunk = 64;
 __host__ __device__ inline int xcd_chunk_item(int x, int it, int total) {
-    int rounds = total / (kNumXcd * kShadeChunk);
-    if (it < rounds * kShadeChunk) return (it / kShadeChunk * kNumXcd + x) * kShadeChunk + it % kShadeChunk;
+    int rounds = total / (kNumXcd * kShadeChunk), round = it / kShadeChunk;
+    if (round < rounds) {
+        int chunk = (x + (round >> 1) + (round >> 3)) % kNumXcd;
+        return (round * kNumXcd + chunk) * kShadeChunk + it % kShadeChunk;
+    }
     int first = rounds * (kNumXcd * kShadeChunk);
     return first + xcd_share(x, total - first).first + (it - rounds * kShadeChunk);
 }

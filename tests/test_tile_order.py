@@ -69,6 +69,19 @@ def test_batch_of_equal_views(owners, views, tiles):
     assert per.max() - per.min() <= 1
 
 
+@pytest.mark.parametrize("width", [1920, 2048, 3840, 4096, 6144, 8192, 10240, 16384])
+@pytest.mark.parametrize("height", [1024, 2160, 4096])
+def test_columns_of_an_image(owners, width, height):
+    """In the shading pass's chunks every XCD gets about its eighth of each quarter of the columns.
+    (1024 rows of 8192 pixels are 512 chunks, 16 of each quarter to an XCD: up to 4 more or less.)"""
+    tx, ty = -(-width // 32), -(-height // 8)
+    o = owners(1, tx * ty)
+    quarter = np.arange(tx * ty) % tx * 4 // tx
+    for x in range(8):
+        share = np.bincount(quarter[o == x], minlength=4) / np.bincount(quarter) * 8
+        assert (abs(share - 1) < 0.25).all(), (x, share)
+
+
 # views of one size, of sizes within twice the mean, and uneven ones
 @pytest.mark.parametrize("sizes,chunks", [([(256, 256)] * 16, 0), ([(320, 240)] * 8, 0), ([(64, 48)], 0),
                                           ([(64, 64)] * 3 + [(128, 64)] * 3, 0), ([(256, 256)] * 8 + [(512, 512)], 1),
