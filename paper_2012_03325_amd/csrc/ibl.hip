@@ -888,10 +888,14 @@ IblPlan ibl_plan(int S, const epb_ibl_params &p) {
     q.off_src = take((size_t)nsrc * 16);
     q.off_tab = take((size_t)nsrc * 16);
     q.off_part = take((size_t)chunks * nout * 8 * 4);
-    // environment mip chain for filtered importance sampling: levels 1 .. last (a quarter of
-    // this; the scratch keeps the size it had with a copy of level 0, so that filtered sampling
-    // never asks for less than plain sampling, as callers may assume)
-    q.off_chain = take(q.fis ? (size_t)8 * S * S * 16 : 0);
+    // The environment as the prefilter reads it: RGB pairs for plain sampling (24 bytes a texel,
+    // 36 MiB at 6x512^2, 2304 MiB at 6x4096^2; rows of packed RGB took half), levels 1 .. last of the
+    // mip chain for filtered sampling (16 bytes, a third as many texels).  The same room for both,
+    // so that filtered sampling, which adds the partial sums, never asks for less than plain
+    // sampling of the same sizes.
+    size_t pairs = q.pref_levels > 1 ? (size_t)6 * S * S * sizeof(RgbPair) : 0;
+    size_t chain = q.fis ? (size_t)chain_offset_pow2(S, q.chain_last + 1) * sizeof(float4) : 0;
+    q.off_env = take(pairs > chain ? pairs : chain);
     // the prefilter's GGX sample tables and partial sums of every level
     size_t part = 0;
     for (int m = 1; q.fis && m < q.pref_levels; ++m) {  // (level 0 has roughness 0: no samples)
@@ -899,7 +903,6 @@ IblPlan ibl_plan(int S, const epb_ibl_params &p) {
         part += (size_t)prefilter_chunks(sm) * 6 * sm * sm * 8 * 4;
     }
     q.off_ggx = take(q.pref_levels > 1 ? (size_t)q.pref_levels * q.pref_samples * 16 : 0);  // a table per level
-    q.off_rgb = take(!q.fis && q.pref_levels > 1 ? (size_t)6 * S * S * sizeof(RgbPair) : 0);
     q.off_ppart = take(part);
     q.bytes = off;
     return q;
@@ -916,8 +919,8 @@ hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr,
     a.src_tex = (float4 *)(sc + q.off_src);
     a.src_tab = (float4 *)(sc + q.off_tab);
     a.part = (float *)(sc + q.off_part);
-    a.chain = (float4 *)(sc + q.off_chain);
-    a.rgb = (RgbPair *)(sc + q.off_rgb);
+    a.chain = (float4 *)(sc + q.off_env);
+    a.rgb = (RgbPair *)(sc + q.off_env);
     a.ggx = (float4 *)(sc + q.off_ggx);
     a.irr_out = (float4 *)irr;
     a.lut_out = (float2 *)lut;
