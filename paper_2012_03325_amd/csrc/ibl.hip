@@ -314,10 +314,10 @@ __device__ __forceinline__ float4 mean_of_children(const float4 (&L)[4], const f
 // face, are made first, side by side (level after level they are a serial chain: 17 us
 // for the preparing launch of a 6x64^2 cube).
 constexpr int kChainStep = 5;
-// Faces a block takes where the chain step starts from faces of size S: one while that gives
-// few blocks, which the six faces' loads and the solid angles then bound (preparing launch of a
-// 6x64^2 cube 11.9 us with six, 8.5 with one; 6x256^2 12.2 / 11.7); six where the solid angles are
-// much of the work (6x512^2 26 / 34 us).
+// Faces a block takes where the chain starts from faces of size S (the later steps start from
+// 128 at most, and take one): one while that gives few blocks, which the six faces' loads and
+// the solid angles then bound (preparing launch of a 6x64^2 cube 11.9 us with six, 8.5 with one;
+// 6x256^2 12.2 / 11.7); six where the solid angles are much of the work (6x512^2 26 / 34 us).
 __host__ __device__ inline int chain_faces(int S) { return S > 256 ? 6 : 1; }
 struct ChainLds {
     float4 a[6 * 16 * 16], b[6 * 8 * 8];
@@ -792,7 +792,7 @@ __global__ void __launch_bounds__(256) k_ibl_prepare(const IblArgs a) {
 
 __global__ void __launch_bounds__(256) k_env_chain(const IblArgs a, int first) {
     __shared__ ChainLds sm;
-    env_chain_block((int)blockIdx.x, a.env, a.chain, a.S, first, a.chain_last, chain_faces(a.S >> first), sm);
+    env_chain_block((int)blockIdx.x, a.env, a.chain, a.S, first, a.chain_last, 1, sm);
 }
 
 // Rounds of 8 heavy_run prefilter blocks and 8 light_run others: the two kinds are
@@ -984,7 +984,7 @@ hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr,
     else hipLaunchKernelGGL(k_ibl_prepare<false>, dim3(first), dim3(256), 0, s, a);
     for (int k = kChainStep; q.fis && k < q.chain_last; k += kChainStep) {
         int Sk = q.S >> k, w = Sk < 32 ? 1 : Sk / 32;
-        hipLaunchKernelGGL(k_env_chain, dim3(w * w * (6 / chain_faces(Sk))), dim3(256), 0, s, a, k);
+        hipLaunchKernelGGL(k_env_chain, dim3(w * w * 6), dim3(256), 0, s, a, k);
     }
     if (q.fis) hipLaunchKernelGGL(k_ibl_integrate<true>, dim3(grid), dim3(256), lds, s, a);
     else hipLaunchKernelGGL(k_ibl_integrate<false>, dim3(grid), dim3(256), lds, s, a);
