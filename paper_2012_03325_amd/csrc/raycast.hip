@@ -86,10 +86,9 @@ __global__ void __launch_bounds__(256) k_sphere_records(const RayScene s, const 
     rec[k] = q;
 }
 
-// A wavefront's lanes cover 8 x 8 pixels, each lane PPT pixels of one column (8
-// rows apart), and a workgroup NX x NY wavefronts; kLoads spheres per thread are
+// A wavefront's lanes cover LX x 64 / LX pixels, each lane PPT pixels of one column
+// (64 / LX rows apart), and a workgroup NX x NY wavefronts; kLoads spheres per thread are
 // tested against the workgroup's region between two barriers.
-constexpr int kRayLx = 8, kRayLy = 64 / kRayLx;
 
 // Ray-independent terms of a sphere that a wavefront will intersect.
 struct alignas(16) RayCand {
@@ -101,12 +100,12 @@ __device__ __forceinline__ float from_lane(float v, int lane) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
 
-template <typename TG, int PPT, int NX, int NY, int kLoads>
+template <typename TG, int LX, int PPT, int NX, int NY, int kLoads>
 __global__ void __launch_bounds__(64 * NX *NY) k_raycast(const RayScene s, const RayCam c,
                                                          const SphereRec *__restrict__ rec, RayOut out) {
 #pragma clang fp contract(off)
     constexpr int kWaves = NX * NY, kThreads = 64 * kWaves;
-    constexpr int kRayTy = kRayLy * PPT, kRx = NX * kRayLx, kRy = NY * kRayTy;
+    constexpr int kRayLx = LX, kRayLy = 64 / LX, kRayTy = kRayLy * PPT, kRx = NX * kRayLx, kRy = NY * kRayTy;
     constexpr int kGroup = kThreads * kLoads;  // spheres tested between two barriers
     constexpr int kList = kGroup + 512;
     __shared__ unsigned short list[kList];
@@ -326,10 +325,10 @@ __global__ void __launch_bounds__(64 * NX *NY) k_raycast(const RayScene s, const
     }
 }
 
-template <typename TG, int PPT, int NX, int NY, int kLoads>
+template <typename TG, int LX, int PPT, int NX, int NY, int kLoads>
 static void go_raycast(const RayScene &s, const RayCam &c, const RayOut &out, const SphereRec *rec, hipStream_t st) {
-    int regions = ceil_div(c.W, NX * kRayLx) * ceil_div(c.H, NY * kRayLy * PPT);
-    hipLaunchKernelGGL((k_raycast<TG, PPT, NX, NY, kLoads>), dim3(regions), dim3(64 * NX * NY), 0, st, s, c, rec, out);
+    int regions = ceil_div(c.W, NX * LX) * ceil_div(c.H, NY * (64 / LX) * PPT);
+    hipLaunchKernelGGL((k_raycast<TG, LX, PPT, NX, NY, kLoads>), dim3(regions), dim3(64 * NX * NY), 0, st, s, c, rec, out);
 }
 
 hipError_t launch_raycast(const RayScene &s, const RayCam &c, const RayOut &out, epb_dtype dtype, void *scratch,
@@ -342,11 +341,17 @@ hipError_t launch_raycast(const RayScene &s, const RayCam &c, const RayOut &out,
     // 8 x 8 tile and the workgroup's eight wavefronts sharing one region test win (1920x1080, 16384
     // spheres: 89 us against 99; 2048 spheres equal).
     if (s.n <= 1024 && (size_t)c.W * c.H >= (size_t)1 << 20) {
-        if (dtype == EPB_F32) go_raycast<float, 2, 2, 2, 2>(s, c, out, rec, st);
-        else go_raycast<__half, 2, 2, 2, 2>(s, c, out, rec, st);
+        // Regions of 32 x 16 pixels where attributes are written, so that a workgroup fills whole
+        // 128-byte lines of every plane: neighbouring regions belong to different XCDs, which write
+        // parts of a line one by one (3840x2160 G-buffer of the plane alone 57 us with regions of 16 x
+        // 32, 46 so, with 512 spheres 75 and 66).  A depth map keeps the narrower cone of 8 x 16 pixels
+        // (2048^2, 512 spheres: 30.5 us, 33.9 with 16 x 8).
+        if (!out.normal) go_raycast<float, 8, 2, 2, 2, 2>(s, c, out, rec, st);
+        else if (dtype == EPB_F32) go_raycast<float, 16, 2, 2, 2, 2>(s, c, out, rec, st);
+        else go_raycast<__half, 16, 2, 2, 2, 2>(s, c, out, rec, st);
     } else {
-        if (dtype == EPB_F32) go_raycast<float, 1, 2, 4, 4>(s, c, out, rec, st);
-        else go_raycast<__half, 1, 2, 4, 4>(s, c, out, rec, st);
+        if (dtype == EPB_F32) go_raycast<float, 8, 1, 2, 4, 4>(s, c, out, rec, st);
+        else go_raycast<__half, 8, 1, 2, 4, 4>(s, c, out, rec, st);
     }
     return hipGetLastError();
 }
