@@ -199,7 +199,7 @@ struct BatchHeader {
     int chunk_first[kStages + 1];   // first chunk of each stage
     int compact;                    // some view takes a compact depth copy (else its stage is not launched)
     int columns[kColumnStages];     // items of the blur kernels, which take columns instead of the stages' tiles
-    int shade_chunks;               // 1: the shading stage deals its tiles to the XCDs in chunks (views of uneven sizes)
+    int shade_chunks;               // 1: the shading stage deals its tiles to the XCDs in chunks (see shade_in_chunks)
 };
 
 // Work counters of the persistent launch, in the device copy of the table; the

@@ -14,7 +14,7 @@
 // 128 measure alike).  At that order the kernel is bound by VALU issue and the
 // texture data path together: 8 waves per SIMD, the shadow patches of all lights
 // fetched ahead of the light loop, or the G-buffer fetched ahead of the depth
-// test gain nothing more.  Batches of about equal views go by contiguous shares instead
+// test gain nothing more.  Batches of small views go by contiguous shares instead
 // (see shade_in_chunks).  Lights travel in the kernel
 // argument segment and are read with scalar loads.
 //

@@ -11,8 +11,8 @@ namespace epb {
 constexpr int kNumXcd = 8;  // MI355X: 256 CUs in 8 accelerator complex dies
 
 // XCD x's contiguous share of `total` items: with one workgroup per item a bijection
-// for any total.  A batch of views of about one size takes it in every stage: an
-// XCD gets whole views, or runs of views, and with them the cheap and the costly parts.
+// for any total.  A batch of small views takes it in every stage: an XCD gets whole
+// views, or runs of views, and with them the cheap and the costly parts.
 struct XcdShare {
     int first, count;
 };
@@ -24,7 +24,7 @@ __host__ __device__ inline XcdShare xcd_share(int x, int total) {
 // The same as the item of workgroup b of nb.
 __host__ __device__ inline int xcd_tile(int b, int nb) { return xcd_share(b % kNumXcd, nb).first + b / kNumXcd; }
 
-// The shading pass's order for one view, and for a batch of uneven views: chunks of
+// The shading pass's order for one view, and for a batch with large views: chunks of
 // kShadeChunk consecutive tiles go to the XCDs in turn, so that every XCD gets its share
 // of the costly rows (a contiguous eighth of the image leaves the XCDs of the sky
 // idle) while neighbouring tiles still share an L2; what does not fill a round of
@@ -47,12 +47,12 @@ __host__ __device__ inline int xcd_chunk_item(int x, int it, int total) {
 }
 
 // Whether a batch's shading takes that order (largest: tiles of its largest view).  Not with
-// views of about one size: a round of chunks is 512 tiles, so that views of 256 or 512 tiles
-// give an XCD the same part of every view (256 views of 256x256 in half storage 397 us, float32
-// 451; 316 and 371 by contiguous shares; 8 of 320x240 45.4 / 41.8).  With a view of more than
-// twice the mean a contiguous share is mostly a part of that view (13 views of up to 1920x1080 in
-// float32 431 us, 422 in chunks; 16 in half storage 359 / 355; at 2.1 times the mean one or
-// the other is ahead by 1 or 2 %).
-inline bool shade_in_chunks(long long largest, int n_views, long long total) { return largest * n_views > 2 * total; }
+// views of up to eight rounds: chunks are then too few to share a view out evenly, and a view
+// of 256 or 512 tiles gives an XCD the same part of every view (without the shift above 256 views of
+// 256x256 in half storage 397 us, float32 451; with it 320 and 376; by contiguous shares 316 and
+// 371; 8 of 320x240 45.4 / 41.8).  With larger views a contiguous share is a part of one view, the
+// sky or the ground (8 of 1920x1080 in float32 532 us, 507 in chunks; 13 of up to 1920x1080 431 /
+// 422; 12 of 1280x720, 3600 tiles, equal).
+inline bool shade_in_chunks(long long largest) { return largest > 8LL * kNumXcd * kShadeChunk; }
 
 }  // namespace epb

@@ -82,13 +82,25 @@ def test_columns_of_an_image(owners, width, height):
         assert (abs(share - 1) < 0.25).all(), (x, share)
 
 
-# views of one size, of sizes within twice the mean, and uneven ones
+@pytest.mark.parametrize("tiles,views", [(256, 256), (512, 64), (300, 100)])
+def test_small_views_beside_a_large_one(owners, tiles, views):
+    """In chunks an XCD's share of each quarter of the small views is about an eighth (a chunk of 64
+    tiles is at least an eighth of such a view: 64 views of 512 tiles are 128 chunks of each quarter,
+    16 of them an XCD's, up to 4 more or less)."""
+    o = owners(1, 8192 + tiles * views)[8192:]
+    quarter = np.arange(o.size) % tiles * 4 // tiles
+    for x in range(8):
+        share = np.bincount(quarter[o == x], minlength=4) / np.bincount(quarter) * 8
+        assert (abs(share - 1) < 0.25).all(), (x, share)
+
+
+# views of up to 4096 tiles of 32 x 8 pixels by contiguous shares, larger ones in chunks
 @pytest.mark.parametrize("sizes,chunks", [([(256, 256)] * 16, 0), ([(320, 240)] * 8, 0), ([(64, 48)], 0),
-                                          ([(64, 64)] * 3 + [(128, 64)] * 3, 0), ([(256, 256)] * 8 + [(512, 512)], 1),
+                                          ([(256, 256)] * 8 + [(512, 512)], 0), ([(1280, 720)] * 3, 0),
+                                          ([(2048, 512)], 0), ([(2048, 513)], 1), ([(1920, 1080)] * 2, 1),
                                           ([(1920, 1080), (1280, 720), (640, 480), (320, 240)] * 3, 1)])
 def test_order_of_a_batch(sizes, chunks):
-    """The shading stage's order in the table's header: contiguous shares, which the test above
-    needs for equal views, unless one view has more than twice the mean's tiles."""
+    """The shading stage's order in the table's header."""
     b = _Batch(sizes)
     assert b.build() == E.EPB_OK
     words = list(C.cast(b.table, C.POINTER(C.c_int32 * 37)).contents)
