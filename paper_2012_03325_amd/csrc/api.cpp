@@ -534,6 +534,14 @@ int epb_raycast(const epb_sphere_scene *scene, const epb_camera *cam, const epb_
     epb::RayCam c{};
     for (int k = 0; k < 12; ++k) c.M[k] = cam->world_to_cam[k];
     for (int k = 0; k < 3; ++k) c.o[k] = -(c.M[k] * c.M[3] + c.M[4 + k] * c.M[7] + c.M[8 + k] * c.M[11]);
+    for (int i = 0; i < 3; ++i) {
+        double row = 0.0;
+        for (int j = 0; j < 3; ++j) {
+            const double *a = c.M + 4 * i, *b = c.M + 4 * j;
+            row += std::fabs(a[0] * b[0] + a[1] * b[1] + a[2] * b[2] - (i == j ? 1.0 : 0.0));
+        }
+        if (row > c.skew) c.skew = row;
+    }
     c.fx = cam->fx; c.fy = cam->fy; c.cx = cam->cx; c.cy = cam->cy;
     c.W = cam->width; c.H = cam->height;
     epb::RayOut o{};

@@ -134,6 +134,7 @@ struct RayScene {
 struct RayCam {
     double M[12];  // row-major [R | t]
     double o[3];   // position, -R^T t
+    double skew;   // bound on the largest eigenvalue of R R^T - 1 (a rotation in float32: about 1e-7)
     double fx, fy, cx, cy;
     int W, H;
 };

@@ -76,12 +76,15 @@ __global__ void __launch_bounds__(256) k_sphere_records(const RayScene s, const 
         y1 = (int)fmax(fmin(ceil(hy) + 2.0, (double)c.H), 0.0);
     }
     // depth of the nearest point, lowered by far more than a hit's rounding error: the hit of a
-    // grazing ray is off by up to sqrt(2^-53) of the distances that enter it, about 1e-8 of them
+    // grazing ray is off by up to sqrt(2^-53) of the distances that enter it, about 1e-8 of them.
+    // The ray parameter t is the depth only as far as R is a rotation: with E = R R^T - 1 the hit
+    // o + t d has the depth t + (E T)_z - t (E v)_z, and t |v| is at most about the distances' sum, so
+    // that t differs from it by less than 3 |E| of them up to |E| = 1/4; above that no bound is used.
     double mag = fabs(cc[0]) + fabs(cc[1]) + fabs(cc[2]) + fabs(c.M[3]) + fabs(c.M[7]) + fabs(c.M[11]) + fabs(r);
     SphereRec q;
     q.x = Short2{(short)x0, (short)-x1};
     q.y = Short2{(short)y0, (short)-y1};
-    q.zmin = (float)(-v[2] - fabs(r) - 4e-6 * mag);
+    q.zmin = c.skew <= 0.25 ? (float)(-v[2] - fabs(r) - (4e-6 + 3.0 * c.skew) * mag) : -__builtin_inff();
     q.pad = 0;
     rec[k] = q;
 }
