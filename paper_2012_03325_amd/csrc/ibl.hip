@@ -81,31 +81,37 @@ __device__ __forceinline__ float segment_sum_compensated(float v, int width) {
 // add, this equals repeated 2x2 weighted halving.  Also writes the source
 // table entry (unit direction, solid angle at size Ss).
 // A segment of lpt lanes (the k x k block rounded up to a power of two, at most
-// 64) per texel (i, j), for all six faces: a solid angle, most of the work, does
-// not depend on the face (6x512^2: 31 us with a segment per face).  Each lane
+// 64) per texel (i, j), for all six faces or for one (see kSourceThreads).  Each lane
 // sums its share of the block with Kahan, the segment adds the lanes' sums
 // compensated.  lpt is uniform.
+// All six faces share their solid angles, most of the work (6x512^2 to 64^2: 31 us with a
+// segment per face); but up to this many threads a face (a wavefront on a quarter of the SIMDs) the segments are few
+// and long, and those of one face are shorter (whole precompute with six faces / one: 6x512^2 to
+// 4^2 200 / 147 us, to 16^2 41.9 / 34.7; 6x256^2 to 2^2 198 / 144; 6x128^2 to 8^2 28.6 / 20.5).
+constexpr int kSourceThreads = 16384;
+template <int kFaces>
 __device__ __forceinline__ void ibl_source_block(int block, const float4 *__restrict__ env, int S, int Ss, int lpt,
                                                  float4 *__restrict__ src, float4 *__restrict__ tab) {
-    int t = block * 256 + (int)threadIdx.x;
+    int nface = Ss * Ss, per = (nface * lpt + 255) / 256;  // blocks of one group of faces
+    int f0 = kFaces < 6 ? block / per * kFaces : 0;
+    int t = (kFaces < 6 ? block % per : block) * 256 + (int)threadIdx.x;
     int o = t / lpt, sub = t - o * lpt;
-    int nface = Ss * Ss;
     // (the segment stays together: nface * lpt threads fill whole segments)
     bool live = o < nface;
     int oc = live ? o : nface - 1;
     int j = oc / Ss, i = oc - j * Ss;
     int k = S / Ss;
     Kahan w{0, 0};
-    Kahan c[6][3] = {};
+    Kahan c[kFaces][3] = {};
     for (int q = sub; q < k * k; q += lpt) {
         int bj = q / k, bi = q - bj * k;
         int ci = i * k + bi, cj = j * k + bj;
-        float4 L[6];
+        float4 L[kFaces];
 #pragma unroll
-        for (int f = 0; f < 6; ++f) L[f] = env[(size_t)f * S * S + (size_t)cj * S + ci];
+        for (int f = 0; f < kFaces; ++f) L[f] = env[(size_t)(f0 + f) * S * S + (size_t)cj * S + ci];
         float dw = k == 1 ? 1.0f : texel_solid_angle(ci, cj, S);
 #pragma unroll
-        for (int f = 0; f < 6; ++f) {
+        for (int f = 0; f < kFaces; ++f) {
             kahan_add(c[f][0], L[f].x * dw);
             kahan_add(c[f][1], L[f].y * dw);
             kahan_add(c[f][2], L[f].z * dw);
@@ -115,14 +121,14 @@ __device__ __forceinline__ void ibl_source_block(int block, const float4 *__rest
     float iw = 1.0f / segment_sum_compensated(kahan_value(w), lpt);
     float dw = texel_solid_angle(i, j, Ss);
 #pragma unroll
-    for (int f = 0; f < 6; ++f) {
+    for (int f = 0; f < kFaces; ++f) {
         float R = segment_sum_compensated(kahan_value(c[f][0]), lpt);
         float G = segment_sum_compensated(kahan_value(c[f][1]), lpt);
         float Bv = segment_sum_compensated(kahan_value(c[f][2]), lpt);
         if (live && sub == 0) {
-            src[f * nface + o] = make_float4(R * iw, G * iw, Bv * iw, 0.0f);
-            v3 d = normalize(cube_texel_dir(f, i, j, Ss));
-            tab[f * nface + o] = make_float4(d.x, d.y, d.z, dw);
+            src[(f0 + f) * nface + o] = make_float4(R * iw, G * iw, Bv * iw, 0.0f);
+            v3 d = normalize(cube_texel_dir(f0 + f, i, j, Ss));
+            tab[(f0 + f) * nface + o] = make_float4(d.x, d.y, d.z, dw);
         }
     }
 }
@@ -757,7 +763,7 @@ struct IblArgs {
     float2 *lut_out;
     GgxLevels lv;
     IblLevel level[8];
-    int source_blocks, env_blocks, ggx_blocks;   // launch 1 (then the mirror levels' blocks)
+    int source_faces, source_blocks, env_blocks, ggx_blocks;  // launch 1 (then the mirror levels' blocks)
     int heavy, light, heavy_run, light_run;      // launch 2: blocks of each kind, and of each in a round / 8
     int partial_blocks, lut_blocks, out_blocks;  // (light = partial_blocks + lut_blocks)
 };
@@ -765,7 +771,10 @@ struct IblArgs {
 template <bool kFis>
 __global__ void __launch_bounds__(256) k_ibl_prepare(const IblArgs a) {
     int b = (int)blockIdx.x;
-    if (b < a.source_blocks) return ibl_source_block(b, a.env, a.S, a.src, a.lpt, a.src_tex, a.src_tab);
+    if (b < a.source_blocks) {
+        if (a.source_faces == 6) return ibl_source_block<6>(b, a.env, a.S, a.src, a.lpt, a.src_tex, a.src_tab);
+        return ibl_source_block<1>(b, a.env, a.S, a.src, a.lpt, a.src_tex, a.src_tab);
+    }
     b -= a.source_blocks;
     if (b < a.env_blocks) {
         if constexpr (kFis) {
@@ -961,7 +970,8 @@ hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr,
         v.blocks = ceil_div(blocks, kNumXcd) * kNumXcd;
         a.heavy += v.blocks;
     }
-    a.source_blocks = ceil_div(q.src * q.src * a.lpt, 256);
+    a.source_faces = q.src * q.src * a.lpt <= kSourceThreads ? 1 : 6;
+    a.source_blocks = ceil_div(q.src * q.src * a.lpt, 256) * (6 / a.source_faces);
     int side = q.S < 32 ? q.S : 32;
     if (q.fis) a.env_blocks = q.chain_last > 0 ? (q.S / side) * (q.S / side) * (6 / chain_faces(q.S)) : 0;
     else a.env_blocks = q.pref_levels > 1 ? ceil_div(n0, 256) : 0;
