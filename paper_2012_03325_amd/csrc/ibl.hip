@@ -403,6 +403,11 @@ __device__ __forceinline__ void env_chain_block(int block, const float4 *__restr
 // repeats itself and is never a lookup's upper row), so that the 2x2 texels of a
 // lookup are 48 bytes in one piece: three loads and mostly one cache line, where
 // rows of packed RGB took four loads and two lines (6x512^2 precompute: 407 us).
+// Not where lookups are few: with up to half a lookup a texel of the environment the copy costs
+// more than it saves, and with up to 32 samples a wavefront's lanes are half idle and wait for
+// no unit (whole precompute, with pairs / without: 6x4096^2, 128^2 in five levels, 1024 samples
+// 1825 / 1496 us, 0.33 lookups; 512^2 in five, 128 samples 2633 / 2809, 0.66; 32^2 in three, 16
+// samples 1067 / 301; 6x1024^2, 512^2 in five, 16 samples 414 / 374, 48 samples 452 / 498).
 struct Rgb {
     float r, g, b;
 };
@@ -417,27 +422,46 @@ __device__ __forceinline__ void env_rgb_block(int block, const float4 *__restric
     sto(dst, (unsigned)o * 24u, RgbPair{Rgb{t.x, t.y, t.z}, Rgb{u.x, u.y, u.z}});
 }
 
-// face_bilinear over these texels, split into its loads and its interpolation (so
-// that a caller can have several lookups' loads in flight): the same coordinates,
-// taps and interpolation, so the same values.
-struct RgbTaps {
+// face_bilinear over the environment's texels or these pairs, split into its loads and its
+// interpolation (so that several lookups' loads can be in flight): the same coordinates, taps
+// and interpolation, so the same values.
+struct TapPlace {
+    unsigned idx;  // upper left texel
+    float wx, wy;
+};
+__device__ __forceinline__ TapPlace tap_place(const FaceDims &g, FaceST f) {
+    float x = clamp_to(fmaf(f.s, g.half, g.off), g.hi);
+    float y = clamp_to(fmaf(f.t, g.half, g.off), g.hi);
+    float x0f = clamp_to(floorf(x), g.hi1), y0f = clamp_to(floorf(y), g.hi1);
+    return TapPlace{__umul24((unsigned)fmaf(f.face, (float)g.S, y0f), (unsigned)g.S) + (unsigned)x0f, x - x0f, y - y0f};
+}
+struct TexelTaps {
+    float4 a, b, c, d;
+    float wx, wy;
+};
+__device__ __forceinline__ TexelTaps env_taps(const float4 *__restrict__ lvl, const FaceDims &g, FaceST f) {
+    TapPlace t = tap_place(g, f);
+    unsigned o0 = t.idx * 16u, o1 = o0 + (unsigned)g.S * 16u;
+    return TexelTaps{ldo(lvl, o0), ldo(lvl + 1, o0), ldo(lvl, o1), ldo(lvl + 1, o1), t.wx, t.wy};
+}
+__device__ __forceinline__ float4 env_value(const TexelTaps &q) {
+    return lerp4(lerp4(q.a, q.b, q.wx), lerp4(q.c, q.d, q.wx), q.wy);
+}
+struct PairTaps {
     float4 v[3];  // a.rgb c.r | c.gb b.rg | b.b d.rgb
     float wx, wy;
 };
-__device__ __forceinline__ RgbTaps rgb_taps(const RgbPair *__restrict__ lvl, const FaceDims &g, FaceST f) {
-    RgbTaps q;
-    float x = clamp_to(fmaf(f.s, g.half, g.off), g.hi);
-    float y = clamp_to(fmaf(f.t, g.half, g.off), g.hi);
-    float x0f = fminf(floorf(x), g.hi1), y0f = fminf(floorf(y), g.hi1);
-    q.wx = x - x0f;
-    q.wy = y - y0f;
-    unsigned idx = __umul24((unsigned)fmaf(f.face, (float)g.S, y0f), (unsigned)g.S) + (unsigned)x0f;
+__device__ __forceinline__ PairTaps env_taps(const RgbPair *__restrict__ lvl, const FaceDims &g, FaceST f) {
+    TapPlace t = tap_place(g, f);
+    PairTaps q;
+    q.wx = t.wx;
+    q.wy = t.wy;
     const float4 *p = reinterpret_cast<const float4 *>(lvl);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) q.v[k] = ldo(p + k, idx * 24u);
+    for (int k = 0; k < 3; ++k) q.v[k] = ldo(p + k, t.idx * 24u);
     return q;
 }
-__device__ __forceinline__ float4 rgb_bilinear(const RgbTaps &q) {
+__device__ __forceinline__ float4 env_value(const PairTaps &q) {
     float4 A = make_float4(q.v[0].x, q.v[0].y, q.v[0].z, 0.0f), C = make_float4(q.v[0].w, q.v[1].x, q.v[1].y, 0.0f);
     float4 B = make_float4(q.v[1].z, q.v[1].w, q.v[2].x, 0.0f), D = make_float4(q.v[2].y, q.v[2].z, q.v[2].w, 0.0f);
     return lerp4(lerp4(A, B, q.wx), lerp4(C, D, q.wx), q.wy);
@@ -471,13 +495,14 @@ __device__ __forceinline__ void ggx_table_block(int block, int m, const GgxLevel
 }
 
 // One wavefront per prefiltered texel of a level (roughness > 0), from level 0
-// of the environment (its RGB pairs): sample k's half vector from the table, its direction l
+// of the environment (or its RGB pairs): sample k's half vector from the table, its direction l
 // the half vector reflected about the texel normal n; with N.L > 0 it adds
 // L(l) N.L and N.L.  A lane takes its samples k and k + 64 together: both
 // lookups' taps are in flight before either is added (the adds keep the order
 // k, k + 64, k + 128, ...), and the next pair's table entries load one
 // iteration ahead, with the current pair's taps.
-__device__ __forceinline__ void prefilter_block(int block, int blocks, const RgbPair *__restrict__ env, int S, int sm,
+template <typename TE>
+__device__ __forceinline__ void prefilter_block(int block, int blocks, const TE *__restrict__ env, int S, int sm,
                                                 const float4 *__restrict__ table, int samples,
                                                 float4 *__restrict__ out) {
     int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -504,10 +529,10 @@ __device__ __forceinline__ void prefilter_block(int block, int blocks, const Rgb
         v3 la = ha * (2.0f * vha) - n, lb = hb * (2.0f * vhb) - n;
         float nla = dot(n, la), nlb = dot(n, lb);
         bool ua = nla > 0.0f, ub = k + 64 < samples && nlb > 0.0f;
-        RgbTaps qa{}, qb{};
-        if (ua) qa = rgb_taps(env, dims, cube_face(la));
-        if (ub) qb = rgb_taps(env, dims, cube_face(lb));
-        float4 La = rgb_bilinear(qa), Lb = rgb_bilinear(qb);
+        decltype(env_taps(env, dims, FaceST{})) qa{}, qb{};
+        if (ua) qa = env_taps(env, dims, cube_face(la));
+        if (ub) qb = env_taps(env, dims, cube_face(lb));
+        float4 La = env_value(qa), Lb = env_value(qb);
         if (ua) {
             kahan_add(r, La.x * nla);
             kahan_add(g, La.y * nla);
@@ -529,31 +554,6 @@ __device__ __forceinline__ void prefilter_block(int block, int blocks, const Rgb
         float iw = 1.0f / W;
         out[o] = make_float4(R * iw, G * iw, Bv * iw, 0.0f);
     }
-}
-
-// face_bilinear split into its loads and its interpolation, so that several lookups'
-// loads can be in flight: the same coordinates, taps and interpolation.
-struct LevelTaps {
-    float4 a, b, c, d;
-    float wx, wy;
-};
-__device__ __forceinline__ LevelTaps level_taps(const float4 *__restrict__ lvl, const FaceDims &g, FaceST f) {
-    LevelTaps q;
-    float x = clamp_to(fmaf(f.s, g.half, g.off), g.hi);
-    float y = clamp_to(fmaf(f.t, g.half, g.off), g.hi);
-    float x0f = clamp_to(floorf(x), g.hi1), y0f = clamp_to(floorf(y), g.hi1);
-    q.wx = x - x0f;
-    q.wy = y - y0f;
-    unsigned idx = __umul24((unsigned)fmaf(f.face, (float)g.S, y0f), (unsigned)g.S) + (unsigned)x0f;
-    unsigned o0 = idx * 16u, o1 = o0 + (unsigned)g.S * 16u;
-    q.a = ldo(lvl, o0);
-    q.b = ldo(lvl + 1, o0);
-    q.c = ldo(lvl, o1);
-    q.d = ldo(lvl + 1, o1);
-    return q;
-}
-__device__ __forceinline__ float4 level_value(const LevelTaps &q) {
-    return lerp4(lerp4(q.a, q.b, q.wx), lerp4(q.c, q.d, q.wx), q.wy);
 }
 
 // Partial sums of a prefiltered level (roughness > 0) with filtered importance
@@ -591,7 +591,7 @@ __device__ __forceinline__ void prefilter_fis_block(int block, const float4 *__r
     constexpr int kFisRun = 2;
     const ConstFloat *tab = as_constant((const float *)table);
     for (int k = k0; k < k1; k += kFisRun) {
-        LevelTaps t0[kFisRun], t1[kFisRun];
+        TexelTaps t0[kFisRun], t1[kFisRun];
         float nl[kFisRun], fl[kFisRun];
 #pragma unroll
         for (int u = 0; u < kFisRun; ++u) {
@@ -606,14 +606,14 @@ __device__ __forceinline__ void prefilter_fis_block(int block, const float4 *__r
             fl[u] = lod - (float)l0;
             if (nl[u] > 0.0f) {
                 FaceST fs = cube_face(l);
-                t0[u] = level_taps(l0 ? chain + chain_offset_pow2(S, l0) : env, face_dims(S >> l0), fs);
-                t1[u] = level_taps(l1 ? chain + chain_offset_pow2(S, l1) : env, face_dims(S >> l1), fs);
+                t0[u] = env_taps(l0 ? chain + chain_offset_pow2(S, l0) : env, face_dims(S >> l0), fs);
+                t1[u] = env_taps(l1 ? chain + chain_offset_pow2(S, l1) : env, face_dims(S >> l1), fs);
             }
         }
 #pragma unroll
         for (int u = 0; u < kFisRun; ++u) {
             if (nl[u] > 0.0f) {
-                float4 L = lerp4(level_value(t0[u]), level_value(t1[u]), fl[u]);
+                float4 L = lerp4(env_value(t0[u]), env_value(t1[u]), fl[u]);
                 kahan_add(r, L.x * nl[u]);
                 kahan_add(g, L.y * nl[u]);
                 kahan_add(b, L.z * nl[u]);
@@ -810,7 +810,7 @@ __global__ void __launch_bounds__(256) k_env_chain(const IblArgs a, int first) {
 // path, so that the others, which only compute, go ahead of it (348 us for 6x512^2, 351
 // without); the filtered prefilter's wavefronts are chains of dependent lookups, and go
 // ahead in longer runs (6x512^2, 1024 samples: 217 us; in runs of 8 without, 238).
-template <bool kFis>
+template <bool kFis, bool kPairs>
 __global__ void __launch_bounds__(256) k_ibl_integrate(const IblArgs a) {
     extern __shared__ float4 lds[];
     int run = kNumXcd * (a.heavy_run + a.light_run);
@@ -824,8 +824,10 @@ __global__ void __launch_bounds__(256) k_ibl_integrate(const IblArgs a) {
                     __builtin_amdgcn_s_setprio(1);
                     prefilter_fis_block(b, a.env, a.chain, a.S, a.chain_last, v.sm, v.table, a.pref_samples, v.chunks,
                                         v.part);
-                } else {
+                } else if constexpr (kPairs) {
                     prefilter_block(b, v.blocks, a.rgb, a.S, v.sm, v.table, a.pref_samples, v.out);
+                } else {
+                    prefilter_block(b, v.blocks, a.env, a.S, v.sm, v.table, a.pref_samples, v.out);
                 }
                 return;
             }
@@ -897,12 +899,20 @@ IblPlan ibl_plan(int S, const epb_ibl_params &p) {
     q.off_src = take((size_t)nsrc * 16);
     q.off_tab = take((size_t)nsrc * 16);
     q.off_part = take((size_t)chunks * nout * 8 * 4);
-    // The environment as the prefilter reads it: RGB pairs for plain sampling (24 bytes a texel,
-    // 36 MiB at 6x512^2, 2304 MiB at 6x4096^2; rows of packed RGB took half), levels 1 .. last of the
-    // mip chain for filtered sampling (16 bytes, a third as many texels).  The same room for both,
-    // so that filtered sampling, which adds the partial sums, never asks for less than plain
+    // What the prefilter reads beside the environment itself: RGB pairs for plain sampling where
+    // they pay (see RgbPair; 24 bytes a texel, 36 MiB at 6x512^2; rows of packed RGB took half),
+    // levels 1 .. last of the mip chain for filtered sampling (16 bytes, a third as many texels).
+    // The room never shrinks with a larger environment, more samples or levels, and is the same
+    // for both, so that filtered sampling, which adds the partial sums, never asks for less than plain
     // sampling of the same sizes.
-    size_t pairs = q.pref_levels > 1 ? (size_t)6 * S * S * sizeof(RgbPair) : 0;
+    size_t texels = (size_t)6 * S * S, lookups = 0;
+    for (int m = 1; m < q.pref_levels; ++m) {
+        size_t sm = (size_t)(q.pref_base >> m);
+        lookups += 6 * sm * sm * q.pref_samples;
+    }
+    size_t most = q.pref_samples > 32 ? 2 * lookups : 0;  // texels of which a copy pays
+    q.pairs = !q.fis && texels <= most;
+    size_t pairs = (texels < most ? texels : most) * sizeof(RgbPair);
     size_t chain = q.fis ? (size_t)chain_offset_pow2(S, q.chain_last + 1) * sizeof(float4) : 0;
     q.off_env = take(pairs > chain ? pairs : chain);
     // the prefilter's GGX sample tables and partial sums of every level
@@ -974,7 +984,7 @@ hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr,
     a.source_blocks = ceil_div(q.src * q.src * a.lpt, 256) * (6 / a.source_faces);
     int side = q.S < 32 ? q.S : 32;
     if (q.fis) a.env_blocks = q.chain_last > 0 ? (q.S / side) * (q.S / side) * (6 / chain_faces(q.S)) : 0;
-    else a.env_blocks = q.pref_levels > 1 ? ceil_div(n0, 256) : 0;
+    else a.env_blocks = q.pairs ? ceil_div(n0, 256) : 0;
     a.ggx_blocks = q.pref_levels > 1 ? ceil_div(q.pref_samples, 256) * q.pref_levels : 0;
     a.out_blocks = ceil_div(nout, 256);
     a.partial_blocks = a.out_blocks * q.chunks;
@@ -996,8 +1006,9 @@ hipError_t launch_precompute_ibl(const IblPlan &q, const float *env, float *irr,
         int Sk = q.S >> k, w = Sk < 32 ? 1 : Sk / 32;
         hipLaunchKernelGGL(k_env_chain, dim3(w * w * 6), dim3(256), 0, s, a, k);
     }
-    if (q.fis) hipLaunchKernelGGL(k_ibl_integrate<true>, dim3(grid), dim3(256), lds, s, a);
-    else hipLaunchKernelGGL(k_ibl_integrate<false>, dim3(grid), dim3(256), lds, s, a);
+    if (q.fis) hipLaunchKernelGGL((k_ibl_integrate<true, false>), dim3(grid), dim3(256), lds, s, a);
+    else if (q.pairs) hipLaunchKernelGGL((k_ibl_integrate<false, true>), dim3(grid), dim3(256), lds, s, a);
+    else hipLaunchKernelGGL((k_ibl_integrate<false, false>), dim3(grid), dim3(256), lds, s, a);
     hipLaunchKernelGGL(k_ibl_final, dim3(final_blocks), dim3(256), 0, s, a);
     if (!lut_rows)
         hipLaunchKernelGGL(k_brdf_lut, dim3(ceil_div(q.lut * q.lut, 4)), dim3(256), 0, s, q.lut, q.lut_samples,

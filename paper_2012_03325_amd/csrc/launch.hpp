@@ -31,6 +31,7 @@ struct IblPlan {
     int lut, lut_samples;
     int chunks;     // split of the irradiance source sum
     int fis;        // filtered importance sampling of the prefilter
+    int pairs;      // plain prefilter from a copy of the environment in pairs of RGB texels
     int chain_last; // last level of the environment mip chain (faces >= 2x2)
     size_t off_src, off_tab, off_part, off_env, off_ggx, off_ppart, bytes;  // scratch layout
 };

@@ -18,3 +18,18 @@ def test_filtered_asks_for_no_less_than_plain(size, pref, levels):
     for irr, samples in ((2, 1), (32, 64), (64, 4096)):
         plain, filtered = (_bytes(size, fis, irr, 64, pref, levels, samples) for fis in (0, 1))
         assert plain > 0 and filtered >= plain
+
+
+SIZES = [8, 16, 32, 64, 128, 256, 512, 1024, 2048, 4096]
+
+
+@pytest.mark.parametrize("fis", [0, 1])
+@pytest.mark.parametrize("pref,levels,samples", [(8, 1, 64), (8, 3, 16), (32, 3, 33), (128, 2, 64), (128, 4, 1024)])
+def test_a_larger_environment_asks_for_no_less(pref, levels, samples, fis):
+    """A buffer sized for the largest environment serves smaller ones too, for more samples fewer."""
+    sizes = [s for s in SIZES if (min(s, pref) >> (levels - 1)) >= 2]
+    asked = [_bytes(s, fis, 32, 8, pref, levels, samples) for s in sizes]
+    assert min(asked) > 0 and asked == sorted(asked)
+    for s in sizes:
+        asked = [_bytes(s, fis, 32, 8, pref, levels, n) for n in (1, 16, 32, 33, 64, 500, 4096)]
+        assert asked == sorted(asked)
