@@ -53,14 +53,14 @@ def log(msg):
 # copy of known size), valid while the kernel's sources hash to the recorded value
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_shade_1080p_traffic.json")
 SHADE_SOURCES = ("paper_2012_03325_amd/csrc/shade.hip", "paper_2012_03325_amd/csrc/shade_tiles.hpp",
-                 "paper_2012_03325_amd/csrc/device_common.hpp",
+                 "paper_2012_03325_amd/csrc/tile_order.hpp", "paper_2012_03325_amd/csrc/device_common.hpp",
                  "paper_2012_03325_amd/csrc/desc.hpp", "include/epb.h")
 
 
 FRAME_VALU_FILE = os.path.join(ROOT, "profiles", "frame_1080p_valu.json")
 FRAME_SOURCES = tuple("paper_2012_03325_amd/csrc/" + f for f in (
     "ssao.hip", "ssao_tiles.hpp", "shade.hip", "shade_tiles.hpp", "post.hip", "post_tiles.hpp",
-    "device_common.hpp", "desc.hpp")) + ("include/epb.h",)
+    "tile_order.hpp", "device_common.hpp", "desc.hpp")) + ("include/epb.h",)
 
 
 def sources_sha256(files) -> str:

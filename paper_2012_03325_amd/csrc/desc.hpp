@@ -94,7 +94,7 @@ struct ShadeDesc {
 
 struct PostDesc {
     int W, H, nl;  // nl = number of pyramid levels >= 1
-    int texel_half;  // pyramid texels are four halves (else float4)
+    int texel_half;  // pyramid texels are four halves (else float4, three floats before the blur)
     int lw[EPB_MAX_BLOOM_LEVELS], lh[EPB_MAX_BLOOM_LEVELS];
     void *raw[EPB_MAX_BLOOM_LEVELS];   // unblurred level texels (RawTexel of the pyramid's)
     void *blur[EPB_MAX_BLOOM_LEVELS];  // blurred level texels

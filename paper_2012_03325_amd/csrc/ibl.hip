@@ -18,9 +18,9 @@
 //    per-lane Kahan sums, compensated wave reduction through cross-lane
 //    shuffles; a lane takes two samples at a time (both lookups' taps in
 //    flight), their half vectors from the level's table one iteration ahead,
-//    the taps from a copy of the environment that holds vertical pairs of RGB
-//    texels (the texture data path bounds this kernel: fewer loads and lines per
-//    lookup).
+//    the taps, where lookups are many, from a copy of the environment that holds
+//    vertical pairs of RGB texels (the texture data path bounds this kernel: fewer
+//    loads and lines per lookup).
 //  * prefilter with filtered importance sampling (taps on the mip level that
 //    matches each sample's footprint): one wavefront per 8x8 tile of output
 //    texels and chunk of the samples; all lanes take the same sample at once,

@@ -22,7 +22,7 @@
 //    and a block that gives up sets the error word, after which no block takes
 //    new work, so the grid always drains.
 //  * one block shape for every stage: 256 threads, the stage's tile function
-//    as in the seven-launch form (SSAO raw and blur on 16 x 16 texel tiles,
+//    as in the form of one launch per stage (SSAO raw and blur on 16 x 16 texel tiles,
 //    composite on four 64 x 8 tiles, one per wavefront).  Per output value
 //    the arithmetic is that of the other forms, so the results are bitwise equal.
 #include "device_common.hpp"
@@ -100,9 +100,9 @@ __device__ __forceinline__ void publish(PersistState *st, int *done, Pending &pd
 }
 
 // Every stage's code in one kernel: it needs at least the largest register
-// count of any stage (the composite's 91-96), and the combined kernel spills
+// count of any stage (the composite's 107 to 111), and the combined kernel spills
 // heavily at 5 waves per SIMD (96 registers), so it runs at 4 waves per SIMD
-// with 128 registers (a few registers still spill).
+// with 128 registers (in float32 20 bytes a lane still spill).
 //
 // A block publishes its finished chunks lazily: when it moves to another stage,
 // before it waits for anything, when its pending list is full and when it

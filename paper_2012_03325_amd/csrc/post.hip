@@ -16,7 +16,7 @@
 //    the upsampled levels to its pixels, applies exposure, the ACES fit,
 //    gamma and 8-bit rounding, and writes one 32-bit RGBA word per pixel
 //    (small images: half a strip per wavefront, see kCompositeHalfStrips).
-//  * pyramid texels are float4, or four halves in the FP16 form.
+//  * pyramid texels are float4 (three floats before the blur), or four halves in the FP16 form.
 //  * every stage has a single-view kernel and a batched kernel that walks the
 //    work items of many views.
 #include "device_common.hpp"
@@ -199,7 +199,7 @@ int post_items(const PostDesc &c, int stage) {
 
 // Up to this many 64 x 8 strips (one and a half wavefronts per SIMD) a wavefront takes half a
 // strip: the chip is not full and a wavefront's own instructions are the time.  A half strip
-// interpolates 60 % of a strip's level rows, so that larger images take whole ones.  Composite
+// interpolates three quarters of a strip's level rows (13 of 17), so that larger images take whole ones.  Composite
 // of 256x256 in float32 5.0 us by strips, 3.6 by halves, quarters gain nothing more (launches
 // bound bloom and tone mapping, 12.9 / 12.1 us); 1003x667 (1344 strips) 5.9 / 5.1; bloom and tone
 // mapping of 1280x720 (1800) 17.3 / 17.6 in half storage, 1920x1080 22.6 / 23.5.

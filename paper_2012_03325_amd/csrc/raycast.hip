@@ -25,8 +25,8 @@
 //
 // Bound: double-precision issue and the latency of the candidate loop where
 // spheres overlap, the G-buffer's stores elsewhere.  Measured per call (512
-// spheres and the plane): 1920x1080 G-buffer 27 us (74.6 MB of stores, 2.8 TB/s),
-// 2048^2 depth map 23 us; 16384 spheres at 1280x720 48 us.  One workgroup per
+// spheres and the plane): 1920x1080 G-buffer 26 us (74.6 MB of stores, 2.9 TB/s),
+// 2048^2 depth map of a light 23 us; 16384 spheres at 1280x720 41 us.  One workgroup per
 // 16x16 pixels that took every box by itself, its list to every pixel and an
 // XCD-contiguous order: 50, 57 and 163 us.
 #include <type_traits>
