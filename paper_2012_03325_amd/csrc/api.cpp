@@ -667,7 +667,7 @@ int epb_batch_build(const epb_view *views, int32_t n_views, const epb_schedule *
     }
     for (int k = 0; k < epb::kColumnStages; ++k) columns[k * (n_views + 1) + n_views] = h.columns[k];
     h.compact = compact;
-    h.shade_chunks = epb::shade_in_chunks(largest) ? 1 : 0;
+    h.shade_chunks = epb::shade_in_chunks(largest, q.blocks_per_cu > 0) ? 1 : 0;
     h.persistent = q.persistent ? 1 : 0;
     h.chunk = q.persistent;
     h.gate = q.wait_limit < 0 ? 0 : 1;

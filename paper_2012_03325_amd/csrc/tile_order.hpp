@@ -52,7 +52,11 @@ __host__ __device__ inline int xcd_chunk_item(int x, int it, int total) {
 // 256x256 in half storage 397 us, float32 451; with it 320 and 376; by contiguous shares 316 and
 // 371; 8 of 320x240 45.4 / 41.8).  With larger views a contiguous share is a part of one view, the
 // sky or the ground (8 of 1920x1080 in float32 532 us, 507 in chunks; 13 of up to 1920x1080 431 /
-// 422; 12 of 1280x720, 3600 tiles, equal).
-inline bool shade_in_chunks(long long largest) { return largest > 8LL * kNumXcd * kShadeChunk; }
+// 422; 12 of 1280x720, 3600 tiles, equal).  Not with grids that loop over the tiles either, where
+// contiguous shares are ahead at every size (16 views of up to 1920x1080, half storage, 8 / 16 / 32
+// workgroups per CU: chunks 479 / 466 / 447 us, shares 437 / 388 / 378).
+inline bool shade_in_chunks(long long largest, bool looping) {
+    return !looping && largest > 8LL * kNumXcd * kShadeChunk;
+}
 
 }  // namespace epb

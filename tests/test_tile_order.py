@@ -100,8 +100,9 @@ def test_small_views_beside_a_large_one(owners, tiles, views):
                                           ([(2048, 512)], 0), ([(2048, 513)], 1), ([(1920, 1080)] * 2, 1),
                                           ([(1920, 1080), (1280, 720), (640, 480), (320, 240)] * 3, 1)])
 def test_order_of_a_batch(sizes, chunks):
-    """The shading stage's order in the table's header."""
+    """The shading stage's order in the table's header: never chunks in a grid that loops."""
     b = _Batch(sizes)
-    assert b.build() == E.EPB_OK
-    words = list(C.cast(b.table, C.POINTER(C.c_int32 * 37)).contents)
-    assert words[36] == chunks
+    for blocks_per_cu in (0, 1, 8):
+        assert b.build(sched=E.epb_schedule(0, 0, 0, blocks_per_cu, 0, 0, 0)) == E.EPB_OK
+        words = list(C.cast(b.table, C.POINTER(C.c_int32 * 37)).contents)
+        assert words[36] == (chunks if blocks_per_cu == 0 else 0)
