@@ -740,10 +740,10 @@ __device__ __forceinline__ void brdf_lut_rows_block(int block, int size, int sam
 // and it runs the prefilter, which the texture data path bounds, beside the
 // irradiance and the BRDF table, which vector issue bounds.  One launch per step and
 // level (ten, with filtered sampling sixteen or more) took 544 us at 6x512^2 and
-// 108 us for the small filtered tables of a 6x64^2 cube, this takes 348 and 43.  At
-// 6x512^2 the preparing launch is 28 us (25 MB read, 38 MB written), the integrals 345
-// (its steps one by one, with row-wise packed texels: 511), bound by vector issue (82 %
-// busy) and the texture data path (89 %), the sums 6.
+// 108 us for the small filtered tables of a 6x64^2 cube, this takes 348 and 38.  At
+// 6x512^2 the preparing launch is 27 us (25 MB read, 38 MB written), the integrals 330
+// under the profiler (its steps one by one, with row-wise packed texels: 511), bound by the
+// texture data path (90 % busy; vector issue 71 %), the sums 5 to 6.
 struct IblLevel {
     int sm, chunks;         // face size; sample chunks (filtered sampling)
     int blocks;             // blocks in the integral launch (padded to whole rounds of XCDs)
