@@ -22,7 +22,11 @@ __host__ __device__ inline XcdShare xcd_share(int x, int total) {
 }
 
 // The same as the item of workgroup b of nb.
-__host__ __device__ inline int xcd_tile(int b, int nb) { return xcd_share(b % kNumXcd, nb).first + b / kNumXcd; }
+__host__ __device__ inline int xcd_tile(int b, int nb) {
+    int q = nb / kNumXcd, r = nb % kNumXcd;
+    int x = b % kNumXcd, local = b / kNumXcd;
+    return x < r ? x * (q + 1) + local : r * (q + 1) + (x - r) * q + local;
+}
 
 // The shading pass's order for one view, and for a batch with large views: chunks of
 // kShadeChunk consecutive tiles go to the XCDs in turn, so that every XCD gets its share

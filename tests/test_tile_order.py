@@ -27,6 +27,7 @@ int main(int argc, char **argv) {
         epb::XcdShare s = epb::xcd_share(x, total);
         for (int it = 0; it < s.count; ++it) {
             int g = chunked ? epb::xcd_chunk_item(x, it, total) : s.first + it;
+            if (!chunked && g != epb::xcd_tile(it * epb::kNumXcd + x, total)) return 3;
             if (g < 0 || g >= total || owner[g] != 255) return 1;
             owner[g] = (unsigned char)x;
         }
